@@ -14,19 +14,12 @@
 
 #include "clbm_host.h"
 #include "clbm_aux_kernels.h"
+#include "clbm_batch.h"
+#include "clbm_multi.h"
 
 namespace clbm {
 
-struct BatchInst {
-    LatticeConst c;
-    unsigned long long buf[2];  // device addresses of the two population buffers
-    unsigned long long snap;    // device address of the (u_x, u_y, T) snapshot
-    int tiles_x, tile_off, tile_count, pad;
-};
-
 constexpr int kBP = 6;  // per-tile partials: du2, u2, dT2, T2, bad, max|u|
-
-__device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // One time step of every instance on the active tile list (grid-stride over tiles); S is
 // the storage type of every instance's populations.
@@ -67,22 +60,6 @@ __global__ void __launch_bounds__(1024) k_batch_step(const BatchInst* __restrict
         }
         }
     }
-}
-
-// Tile k of this workgroup among n active tiles (n when there is none). With at least 8
-// workgroups, the workgroups of XCD x (blockIdx % 8 == x) sweep the x-th of eight
-// contiguous bands of the list (instance by instance, row by row), so the ring nodes that
-// neighbouring tiles of an instance share stay in that XCD's L2.
-__device__ __forceinline__ int banded_tile(int k, int n)
-{
-    const int b = blockIdx.x, G = gridDim.x;
-    if (G < 8) {
-        const int t = b + k * G;
-        return t < n ? t : n;
-    }
-    const int x = b & 7, i = b >> 3, per = (G - x + 7) >> 3, band = (n + 7) >> 3;
-    const int j = i + k * per, t = x * band + j;
-    return j < band && t < n ? t : n;
 }
 
 // Waves per SIMD the LDS tile allows (160 KB per CU), at most four.
@@ -363,6 +340,8 @@ struct clbm_batch {
     int parity;
     long step;
     clbm_batch_launch launch;
+    const MultiShape* multi;   // deeper tiles in place of the default launch, or nullptr
+    int tile_x, tile_y;        // tiles of the list
     hipGraph_t graph;
     hipGraphExec_t gexec;
     int graph_K;
@@ -398,6 +377,14 @@ clbm_batch_launch default_batch_launch()
     L.steps_per_launch = 2;
     L.xcd_bands = 1;
     return L;
+}
+
+// The default launch, with which the library picks the tiles itself (multi_shape).
+bool is_default_launch(const clbm_batch_launch& L)
+{
+    const clbm_batch_launch d = default_batch_launch();
+    return L.tile_x == d.tile_x && L.tile_y == d.tile_y && L.persistent_wgs == d.persistent_wgs &&
+           L.steps_per_launch == d.steps_per_launch && L.xcd_bands == d.xcd_bands;
 }
 
 clbm_status batch_layout(int n, const clbm_params* p, BatchLayout* L)
@@ -459,12 +446,22 @@ void drop_batch_graph(clbm_batch* b)
 clbm_status apply_shape(clbm_batch* b)
 {
     const clbm_batch_launch& L = b->launch;
+    auto tiles = [&](int tx, int ty) -> size_t {
+        size_t n = 0;
+        for (const BatchInst& I : b->inst) n += (size_t)((I.c.nx + tx - 1) / tx) * ((I.c.ny + ty - 1) / ty);
+        return n <= (size_t)b->cap_tiles ? n : 0;
+    };
+    size_t nodes = 0;
+    for (const BatchInst& I : b->inst) nodes += (size_t)I.c.nx * I.c.ny;
+    b->multi = is_default_launch(L) ? multi_shape(tiles, nodes, b->precision) : nullptr;
+    b->tile_x = b->multi ? b->multi->tx : L.tile_x;
+    b->tile_y = b->multi ? b->multi->ty : L.tile_y;
     b->full_host.clear();
     int off = 0;
     for (int i = 0; i < b->n; ++i) {
         BatchInst& I = b->inst[i];
-        const int tx = (I.c.nx + L.tile_x - 1) / L.tile_x;
-        const int ty = (I.c.ny + L.tile_y - 1) / L.tile_y;
+        const int tx = (I.c.nx + b->tile_x - 1) / b->tile_x;
+        const int ty = (I.c.ny + b->tile_y - 1) / b->tile_y;
         I.tiles_x = tx;
         I.tile_off = off;
         I.tile_count = tx * ty;
@@ -525,16 +522,22 @@ const void* step2_for(int vh, int rows)
     return vh == 0 ? step2_rows<S, 0>(rows) : vh == 1 ? step2_rows<S, 1>(rows) : step2_rows<S, 2>(rows);
 }
 
-// The two-step kernel for the batch's storage type, tile height and mix of source terms
-// (viscous heating, source fields) over its instances.
-const void* step2_kernel(const clbm_batch* b)
+// The mix of source terms (viscous heating, source fields) over the instances: MODE of
+// k_batch_step2 and k_batch_multi.
+int source_mix(const clbm_batch* b)
 {
     int vh = 0, qf = 0;
     for (int i = 0; i < b->n; ++i) {
         vh += b->p[i].viscous_heating ? 1 : 0;
         qf += b->inst[i].c.qfield ? 1 : 0;
     }
-    const int mix = qf > 0 ? 2 : vh == 0 ? 0 : (vh == b->n ? 1 : 2);
+    return qf > 0 ? 2 : vh == 0 ? 0 : (vh == b->n ? 1 : 2);
+}
+
+// The two-step kernel for the batch's storage type, tile height and mix of source terms.
+const void* step2_kernel(const clbm_batch* b)
+{
+    const int mix = source_mix(b);
     return b->precision == CLBM_FP16_SHIFTED ? step2_for<__half>(mix, b->launch.tile_y)
                                              : step2_for<float>(mix, b->launch.tile_y);
 }
@@ -555,11 +558,24 @@ const void* diag_kernel(const clbm_batch* b)
 // nodes is covered by kBlock x min(rows, 16) threads, rows looped).
 dim3 tile_block(const clbm_batch* b)
 {
-    return dim3(b->launch.tile_x, std::min(b->launch.tile_y, 1024 / b->launch.tile_x));
+    return dim3(b->tile_x, std::min(b->tile_y, 1024 / b->tile_x));
 }
 
 clbm_status launch_batch_steps(clbm_batch* b, int nsteps)
 {
+    if (b->multi) {
+        const StepSplit split(nsteps, b->multi->steps);
+        for (int k = 0; k < split.launches; ++k) {
+            int parity = b->parity, bands = b->launch.xcd_bands, n = split.steps(k);
+            unsigned inv = multi_inv(*b->multi, n);
+            void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &bands, &n, &inv};
+            CLBM_HIP(hipLaunchKernel(b->multi->batch(b->precision, source_mix(b)), step_grid(b),
+                                     dim3(b->multi->threads), args, 0, b->stream));
+            b->step += n;
+            b->parity ^= 1;
+        }
+        return CLBM_OK;
+    }
     while (nsteps > 0) {
         if (b->launch.steps_per_launch == 2 && nsteps >= 2) {
             int parity = b->parity, bands = b->launch.xcd_bands;
@@ -569,7 +585,7 @@ clbm_status launch_batch_steps(clbm_batch* b, int nsteps)
             b->step += 2;
             nsteps -= 2;
         } else {
-            int parity = b->parity, tx = b->launch.tile_x, ty = b->launch.tile_y;
+            int parity = b->parity, tx = b->tile_x, ty = b->tile_y;
             void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &tx, &ty};
             CLBM_HIP(hipLaunchKernel(step1_kernel(b), step_grid(b), tile_block(b), args, 0, b->stream));
             b->step += 1;
@@ -583,7 +599,7 @@ clbm_status launch_batch_steps(clbm_batch* b, int nsteps)
 
 clbm_status launch_diag(clbm_batch* b, int compare)
 {
-    int parity = b->parity, tx = b->launch.tile_x, ty = b->launch.tile_y;
+    int parity = b->parity, tx = b->tile_x, ty = b->tile_y;
     void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &tx, &ty, &compare, &b->d_part};
     CLBM_HIP(hipLaunchKernel(diag_kernel(b), step_grid(b), tile_block(b), args, 0, b->stream));
     return CLBM_OK;
@@ -599,13 +615,23 @@ clbm_status build_run_graph(clbm_batch* b, int K, double tol, long max_steps)
     const dim3 blk = tile_block(b);
     const dim3 grid = step_grid(b);
     int parity = b->parity, bands = b->launch.xcd_bands;
-    int tx = b->launch.tile_x, ty = b->launch.tile_y;
+    int tx = b->tile_x, ty = b->tile_y;
     clbm_status st = CLBM_OK;
     // The graph is replayed from the same buffer, so it must flip the buffers an even
-    // number of times: K one-step launches, or two-step launches with two one-step
-    // launches in place of one of them when K/2 is odd.
+    // number of times: K one-step launches, two-step launches with two one-step launches
+    // in place of one of them when K/2 is odd, or an even number of deeper launches.
     int pairs = 0, singles = K;
-    if (b->launch.steps_per_launch == 2) {
+    if (b->multi) {
+        const StepSplit split(K, b->multi->steps, true);
+        singles = 0;
+        for (int k = 0; k < split.launches && st == CLBM_OK; ++k) {
+            int n = split.steps(k);
+            unsigned inv = multi_inv(*b->multi, n);
+            void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &bands, &n, &inv};
+            st = add_node(g, &prev, b->multi->batch(b->precision, source_mix(b)), grid, dim3(b->multi->threads), args);
+            parity ^= 1;
+        }
+    } else if (b->launch.steps_per_launch == 2) {
         pairs = (K / 2) % 2 == 0 ? K / 2 : K / 2 - 1;
         singles = K - 2 * pairs;
     }

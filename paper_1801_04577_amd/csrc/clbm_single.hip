@@ -12,6 +12,7 @@
 
 #include "clbm_host.h"
 #include "clbm_aux_kernels.h"
+#include "clbm_multi.h"
 
 namespace clbm {
 
@@ -435,11 +436,38 @@ struct LaunchArgs {
     int a0, a1, a2;
 };
 
-// The launches of n steps: two-step launches while two or more steps remain (when
-// enabled), then single steps. Calls emit(fn, grid, block, args) for each.
+// The deeper tiles that the library takes where two steps per launch are asked for with no
+// tile height of their own, or nullptr. They address the buffer with 32-bit offsets.
+const MultiShape* multi_of(const clbm_handle* h)
+{
+    if (h->launch.steps_per_launch != 2 || h->launch.two_step_rows != 0 || wide_offsets(h->c)) return nullptr;
+    const LatticeConst& c = h->c;
+    return multi_shape(
+        [&](int tx, int ty) { return (size_t)((c.nx + tx - 1) / tx) * ((c.ny + ty - 1) / ty); },
+        (size_t)c.nx * c.ny, h->p.precision);
+}
+
+// The launches of n steps: launches of the deeper tiles, or two-step launches while two or
+// more steps remain (when enabled), then single steps. Calls emit(fn, grid, block, args)
+// for each.
 template <typename Emit>
 clbm_status plan_steps(clbm_handle* h, int n, int from, Emit emit)
 {
+    if (const MultiShape* m = multi_of(h)) {
+        const void* fn = m->single(h->p.precision, lattice_src(h->c));
+        int tiles_x = (h->c.nx + m->tx - 1) / m->tx, total = tiles_x * ((h->c.ny + m->ty - 1) / m->ty);
+        const dim3 grid((unsigned)align_up((size_t)total, 8), 1, 1), block(m->threads, 1, 1);
+        const StepSplit split(n, m->steps);
+        for (int k = 0, cur = from; k < split.launches; ++k, cur ^= 1) {
+            void *src = h->buf[cur], *dst = h->buf[cur ^ 1];
+            int steps = split.steps(k);
+            unsigned inv = multi_inv(*m, steps);
+            void* args[] = {&src, &dst, &h->c, &tiles_x, &total, &steps, &inv};
+            const clbm_status st = emit(fn, grid, block, args);
+            if (st != CLBM_OK) return st;
+        }
+        return CLBM_OK;
+    }
     const bool two = h->launch.steps_per_launch == 2;
     const StepLaunch s1 = plan_step(h->c, h->p.precision, h->launch);
     const Step2Launch s2 = plan_step2(h->c, h->p.precision, h->launch);
@@ -474,6 +502,7 @@ clbm_status plan_steps(clbm_handle* h, int n, int from, Emit emit)
 // Number of launches (buffer flips) of n steps.
 int launches_of(const clbm_handle* h, int n)
 {
+    if (const MultiShape* m = multi_of(h)) return StepSplit(n, m->steps).launches;
     return h->launch.steps_per_launch == 2 ? n / 2 + n % 2 : n;
 }
 
