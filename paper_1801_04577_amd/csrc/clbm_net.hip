@@ -27,231 +27,12 @@
 #include <new>
 #include <vector>
 
+#include "clbm_conv.h"
 #include "clbm_host.h"
 
 namespace clbm {
 
-typedef __bf16 bf16;
-typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kLayers = 15;
-constexpr int kKChunk = 32;  // K per MFMA (one 3x3 tap, 32 input channels)
-
-__device__ __forceinline__ float bf2f(bf16 v) { return (float)v; }
-__device__ __forceinline__ bf16 f2bf(float v) { return (bf16)v; }
-
-// ---------------------------------------------------------------------------
-// Implicit-GEMM 3x3 convolution (zero padding 1), one output pixel row of the GEMM
-// per image pixel: M = B*H*W pixels, N = output channels, K = 9 taps x Cin.
-// A workgroup of 4 waves covers 64 pixels x (16*NB) channels; each wave 16 pixels.
-// MFMA 16x16x32 operand layout: lane l holds row (l % 16) of A and column (l % 16)
-// of B, elements k = 8*(l/16) .. 8*(l/16)+7; the result holds column (l % 16),
-// rows 4*(l/16) .. 4*(l/16)+3.
-// mode 0: y = bf16(relu(acc + bias)); mode 1: y = bf16(acc) (input gradients);
-// mode 2: fp32 NCHW output yf = acc + bias (network output, n < N only).
-// ---------------------------------------------------------------------------
-template <int NB, int MP>
-__global__ void __launch_bounds__(256) k_conv(const bf16* __restrict__ x, int xC, int xoff, int Cin,
-                                              const bf16* __restrict__ w,
-                                              const float* __restrict__ bias, int N, int H, int W,
-                                              int mode, bf16* __restrict__ y, int yC, int yoff,
-                                              float* __restrict__ yf)
-{
-    // A wave owns MP blocks of 16 pixels and NB blocks of 16 output channels: per tap and
-    // 32-channel chunk it loads MP activation and NB weight fragments and issues MP x NB
-    // MFMAs, each fragment reused NB (or MP) times from registers.
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int HW = H * W;
-    const int p0 = (blockIdx.x * 4 + wave) * 16 * MP;
-    const int n0 = blockIdx.y * (16 * NB);
-    const int kq = (lane >> 4) * 8;
-    int pb[MP], py[MP], px[MP];
-#pragma unroll
-    for (int j = 0; j < MP; ++j) {
-        const int pa = p0 + 16 * j + (lane & 15);
-        pb[j] = pa / HW;
-        const int rem = pa - pb[j] * HW;
-        py[j] = rem / W;
-        px[j] = rem - py[j] * W;
-    }
-    f32x4 acc[MP][NB];
-#pragma unroll
-    for (int j = 0; j < MP; ++j)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[j][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16x8 zero = {};
-    for (int tap = 0; tap < 9; ++tap) {
-        const bf16* xs[MP];
-        bool in[MP];
-#pragma unroll
-        for (int j = 0; j < MP; ++j) {
-            const int sy = py[j] + tap / 3 - 1, sx = px[j] + tap % 3 - 1;
-            in[j] = sy >= 0 && sy < H && sx >= 0 && sx < W;
-            // clamped source so the address is valid even where the value is not used
-            const int cy = min(max(sy, 0), H - 1), cx = min(max(sx, 0), W - 1);
-            xs[j] = x + (size_t)(pb[j] * HW + cy * W + cx) * xC + xoff + kq;
-        }
-        for (int c0 = 0; c0 < Cin; c0 += kKChunk) {
-            bf16x8 a[MP];
-#pragma unroll
-            for (int j = 0; j < MP; ++j) {
-                a[j] = *reinterpret_cast<const bf16x8*>(xs[j] + c0);
-                if (!in[j]) a[j] = zero;
-            }
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int n = n0 + 16 * nb + (lane & 15);
-                const bf16x8 bw =
-                    *reinterpret_cast<const bf16x8*>(w + ((size_t)n * 9 + tap) * Cin + c0 + kq);
-#pragma unroll
-                for (int j = 0; j < MP; ++j)
-                    acc[j][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], bw, acc[j][nb], 0, 0, 0);
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < MP; ++j)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int n = n0 + 16 * nb + (lane & 15);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int p = p0 + 16 * j + 4 * (lane >> 4) + v;
-            float r = acc[j][nb][v];
-            if (mode == 2) {
-                if (n < N) {
-                    const int bb = p / HW, rr = p - bb * HW;
-                    yf[((size_t)bb * N + n) * HW + rr] = r + bias[n];
-                }
-            } else if (n < N) {
-                if (mode == 0) r = fmaxf(r + bias[n], 0.f);
-                y[(size_t)p * yC + yoff + n] = f2bf(r);
-            }
-        }
-    }
-}
-
-// The same convolution with both operands staged in LDS. A workgroup owns a block of
-// BH x BW pixels of one image (BH = 256 / BW; wave w owns pixels 64 w .. 64 w + 63 of the
-// block in row-major order, as four MFMA blocks of 16) and 16 NB output channels. Per
-// chunk of 32 input channels it stages the block with its one-pixel halo and the weights
-// of the nine taps in LDS, pixel-major (resp. channel-major) with the 32 channels of the
-// chunk contiguous, so each tap reads both operands from LDS at compile-time offsets:
-// an activation is fetched from memory once per chunk instead of once per tap, and a
-// weight once per workgroup instead of once per wave.
-constexpr int kCvLd = 32;   // LDS row: the 32 channels of a chunk
-
-template <int NB, int BW>
-__global__ void __launch_bounds__(256) k_conv_lds(const bf16* __restrict__ x, int xC, int xoff, int Cin,
-                                                  const bf16* __restrict__ w,
-                                                  const float* __restrict__ bias, int N, int H, int W,
-                                                  int mode, bf16* __restrict__ y, int yC, int yoff,
-                                                  float* __restrict__ yf)
-{
-    constexpr int BH = 256 / BW, HX = BW + 2, HY = BH + 2, NPIX = HX * HY, NC = 16 * NB;
-    __shared__ __attribute__((aligned(16))) bf16 sa[NPIX * kCvLd];
-    __shared__ __attribute__((aligned(16))) bf16 sw[9 * NC * kCvLd];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bx_n = W / BW, by_n = H / BH;
-    const int bxi = blockIdx.x % bx_n, byi = (blockIdx.x / bx_n) % by_n, bimg = blockIdx.x / (bx_n * by_n);
-    const int x0 = bxi * BW, y0 = byi * BH;
-    const int n0 = blockIdx.y * NC;
-    const int r16 = lane & 15, k8 = (lane >> 4) * 8;
-    // LDS element of the A row of each of the wave's four pixel blocks at tap 0 (the
-    // top-left neighbour); tap t adds ((t / 3) HX + t % 3) rows
-    int abase[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int q = wave * 64 + 16 * j + r16;
-        abase[j] = ((q / BW) * HX + (q % BW)) * kCvLd + k8;
-    }
-    f32x4 acc[4][NB];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[j][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16x8 zero = {};
-    // The next chunk's operands are loaded into registers while the current one is
-    // multiplied from LDS.
-    constexpr int NA = (NPIX * 4 + 255) / 256, NWT = (9 * NC * 4 + 255) / 256;
-    bf16x8 ra[NA], rw[NWT];
-    auto load_chunk = [&](int c0) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int t = tid + 256 * i;
-            ra[i] = zero;
-            if (t < NPIX * 4) {
-                const int px = t >> 2, oct = t & 3;
-                const int hy = px / HX, hx = px - hy * HX;
-                const int sy = y0 + hy - 1, sx = x0 + hx - 1;
-                if (sy >= 0 && sy < H && sx >= 0 && sx < W)
-                    ra[i] = *reinterpret_cast<const bf16x8*>(x + ((size_t)(bimg * H + sy) * W + sx) * xC + xoff + c0 + 8 * oct);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < NWT; ++i) {
-            const int t = tid + 256 * i;
-            if (t < 9 * NC * 4) {
-                const int oct = t & 3, rest = t >> 2;   // rest = tap * NC + channel
-                const int tap = rest / NC, nn = rest - tap * NC;
-                rw[i] = *reinterpret_cast<const bf16x8*>(w + ((size_t)(n0 + nn) * 9 + tap) * Cin + c0 + 8 * oct);
-            }
-        }
-    };
-    load_chunk(0);
-    for (int c0 = 0; c0 < Cin; c0 += kKChunk) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int t = tid + 256 * i;
-            if (t < NPIX * 4) *reinterpret_cast<bf16x8*>(&sa[(t >> 2) * kCvLd + 8 * (t & 3)]) = ra[i];
-        }
-#pragma unroll
-        for (int i = 0; i < NWT; ++i) {
-            const int t = tid + 256 * i;
-            if (t < 9 * NC * 4) *reinterpret_cast<bf16x8*>(&sw[(t >> 2) * kCvLd + 8 * (t & 3)]) = rw[i];
-        }
-        __syncthreads();
-        if (c0 + kKChunk < Cin) load_chunk(c0 + kKChunk);
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            const int off = ((tap / 3) * HX + tap % 3) * kCvLd;
-            bf16x8 a[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a[j] = *reinterpret_cast<const bf16x8*>(&sa[abase[j] + off]);
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const bf16x8 bw = *reinterpret_cast<const bf16x8*>(&sw[(tap * NC + 16 * nb + r16) * kCvLd + k8]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[j][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], bw, acc[j][nb], 0, 0, 0);
-            }
-        }
-        __syncthreads();  // the next chunk overwrites the tiles
-    }
-    const int HW = H * W;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int n = n0 + 16 * nb + r16;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int q = wave * 64 + 16 * j + 4 * (lane >> 4) + v;
-            const int p = (bimg * H + y0 + q / BW) * W + x0 + q % BW;
-            float r = acc[j][nb][v];
-            if (mode == 2) {
-                if (n < N) {
-                    const int bb = p / HW, rr = p - bb * HW;
-                    yf[((size_t)bb * N + n) * HW + rr] = r + bias[n];
-                }
-            } else if (n < N) {
-                if (mode == 0) r = fmaxf(r + bias[n], 0.f);
-                y[(size_t)p * yC + yoff + n] = f2bf(r);
-            }
-        }
-    }
-}
 
 // Weight gradient of one 3x3 convolution over a range of pixels (split-K):
 // part[s][co][tap][ci] = sum over the pixels p of split s of dz[p][co] * x[src(p,tap)][ci],
@@ -436,32 +217,6 @@ __global__ void __launch_bounds__(256) k_bias_reduce(const float* __restrict__ p
         __syncthreads();
     }
     if (t == 0) g[c] = lds[0];
-}
-
-// Canonical FP32 weights -> BF16 forward layout wf[n][tap][ci] (n < Npad, ci < CinPad,
-// zeros outside the real sizes) and the input-gradient layout wb[ci][tap'][co] with
-// tap' = 8 - tap (the transposed, flipped kernel).
-__global__ void k_weight_prep(const float* __restrict__ Wc, int Cout, int Cin, int NoutPad,
-                              int CinPad, int CoutKPad, bf16* __restrict__ wf, bf16* __restrict__ wb)
-{
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nf = NoutPad * 9 * CinPad;
-    if (k < nf) {
-        const int n = k / (9 * CinPad), r = k - n * 9 * CinPad;
-        const int tap = r / CinPad, ci = r - tap * CinPad;
-        const float v = (n < Cout && ci < Cin) ? Wc[((size_t)n * Cin + ci) * 9 + tap] : 0.f;
-        wf[k] = f2bf(v);
-    }
-    if (wb) {
-        const int nb = CinPad * 9 * CoutKPad;
-        if (k < nb) {
-            const int ci = k / (9 * CoutKPad), r = k - ci * 9 * CoutKPad;
-            const int tp = r / CoutKPad, co = r - tp * CoutKPad;
-            const int tap = 8 - tp;
-            const float v = (co < Cout && ci < Cin) ? Wc[((size_t)co * Cin + ci) * 9 + tap] : 0.f;
-            wb[k] = f2bf(v);
-        }
-    }
 }
 
 // fp32 NCHW input planes -> bf16 NHWC with zero channel padding.
@@ -721,8 +476,6 @@ struct TView {
 struct Layer {
     int cin, cout;       // real sizes
     int cin_pad;         // K channels (multiple of 32)
-    int nout_pad;        // forward N (multiple of 16 * NB)
-    int nb;              // 16-channel blocks per wave in the forward
     int cout_kpad;       // K channels of the input-gradient convolution (multiple of 32)
     int H, W;            // resolution it runs at
     size_t woff, boff;   // offsets of W and b in the canonical vector
@@ -849,8 +602,6 @@ void layout_net(clbm_net* n, Alloc& a)
         l.cin = cin_[k];
         l.cout = cout_[k];
         l.cin_pad = round_up(l.cin, 32);
-        l.nb = (l.cout % 64 == 0) ? 4 : (l.cout % 32 == 0 ? 2 : 1);
-        l.nout_pad = round_up(l.cout, 16 * l.nb);
         l.cout_kpad = round_up(l.cout, 32);
         l.H = H / res_[k];
         l.W = W / res_[k];
@@ -858,7 +609,7 @@ void layout_net(clbm_net* n, Alloc& a)
         off += (size_t)l.cout * l.cin * 9;
         l.boff = off;
         off += l.cout;
-        l.wf = a.take<bf16>((size_t)l.nout_pad * 9 * l.cin_pad);
+        l.wf = a.take<bf16>((size_t)l.cout_kpad * 9 * l.cin_pad);
         l.wb = k == 0 ? nullptr : a.take<bf16>((size_t)l.cin_pad * 9 * l.cout_kpad);
     }
     n->nparams = off;
@@ -942,47 +693,98 @@ clbm_status upsample_bwd(clbm_net* n, TView dy, int C, int H, int W, TView dx)
     return CLBM_OK;
 }
 
-clbm_status conv_launch(clbm_net* n, const Layer& l, TView in, int cin_pad, const bf16* w,
-                        const float* bias, int N, int nb, int npad, int mode, TView out, float* yf)
+template <int R, int CW, int PX, int PY, int NH>
+clbm_status launch_rows(clbm_net* n, const ConvArgs& a)
 {
-    const int P = n->d.batch * l.H * l.W;
-    int xC = in.C, xoff = in.off, Cin = cin_pad, H = l.H, W = l.W, yC = out.C, yoff = out.off;
-    const bf16* x = in.p;
-    bf16* y = out.p;
-    void* args[] = {&x, &xC, &xoff, &Cin, (void*)&w, (void*)&bias, &N, &H, &W, &mode, &y, &yC, &yoff, &yf};
-    // LDS-staged kernel: pixel blocks of 256 (BW = 64, 32 or 16 columns) that tile the image
-    const int bw = W >= 64 ? 64 : W;
-    if ((nb == 4 || nb == 2) && (bw == 64 || bw == 32 || bw == 16) && W % bw == 0 && H % (256 / bw) == 0) {
-        const void* fl = nb == 4 ? (bw == 64 ? (const void*)&k_conv_lds<4, 64> : bw == 32 ? (const void*)&k_conv_lds<4, 32> : (const void*)&k_conv_lds<4, 16>)
-                                 : (bw == 64 ? (const void*)&k_conv_lds<2, 64> : bw == 32 ? (const void*)&k_conv_lds<2, 32> : (const void*)&k_conv_lds<2, 16>);
-        CLBM_HIP(hipLaunchKernel(fl, dim3(P / 256, npad / (16 * nb)), dim3(256), args, 0, n->stream));
-        return CLBM_OK;
-    }
-    // four 16-pixel blocks per wave where the pixel count allows (it is a multiple of 64)
-    const int mp = P % 256 == 0 ? 4 : 1;
-    const dim3 grid(P / (64 * mp), npad / (16 * nb));
-    const void* fn =
-        mp == 4 ? (nb == 4 ? reinterpret_cast<const void*>(&k_conv<4, 4>)
-                  : nb == 2 ? reinterpret_cast<const void*>(&k_conv<2, 4>)
-                            : reinterpret_cast<const void*>(&k_conv<1, 4>))
-                : (nb == 4 ? reinterpret_cast<const void*>(&k_conv<4, 1>)
-                  : nb == 2 ? reinterpret_cast<const void*>(&k_conv<2, 1>)
-                            : reinterpret_cast<const void*>(&k_conv<1, 1>));
-    CLBM_HIP(hipLaunchKernel(fn, grid, dim3(256), args, 0, n->stream));
+    const int B = a.P / (a.H * a.W);
+    const size_t blocks = (size_t)((a.W + 16 * PX - 1) / (16 * PX)) * ((a.H + R * PY - 1) / (R * PY)) * B;
+    hipLaunchKernelGGL((k_conv_rows<R, CW, PX, PY, NH>), dim3((unsigned)blocks, (a.N + 32 * CW - 1) / (32 * CW)),
+                       dim3(64 * CW * PX * PY), 0, n->stream, a);
+    CLBM_HIP(hipGetLastError());
     return CLBM_OK;
+}
+
+template <int MP, int NG, int NH>
+clbm_status launch_taps(clbm_net* n, const ConvArgs& a)
+{
+    const int waves = (a.P + 16 * MP - 1) / (16 * MP) * ((a.N + 32 * NG - 1) / (32 * NG));
+    hipLaunchKernelGGL((k_conv_taps<MP, NG, NH>), dim3((waves + 3) / 4), dim3(256), 0, n->stream, a);
+    CLBM_HIP(hipGetLastError());
+    return CLBM_OK;
+}
+
+// Whether a layer accumulates with the chunk outermost: images that 256-pixel blocks of 64,
+// 32 or 16 columns tile. The order fixes the rounding of every output, so it depends on
+// the image alone. One chunk gives both orders the same.
+bool chunk_order(int H, int W)
+{
+    const int bw = W >= 64 ? 64 : W;
+    return (bw == 64 || bw == 32 || bw == 16) && W % bw == 0 && H % (256 / bw) == 0;
+}
+
+clbm_status conv_launch(clbm_net* n, const Layer& l, TView in, int cin_pad, const bf16* w,
+                        const float* bias, int N, int mode, TView out, float* yf)
+{
+    ConvArgs a;
+    a.x = in.p;
+    a.xC = in.C;
+    a.xoff = in.off;
+    a.Cin = cin_pad;
+    a.w = w;
+    a.bias = bias;
+    a.N = N;
+    a.H = l.H;
+    a.W = l.W;
+    a.P = n->d.batch * l.H * l.W;
+    a.mode = mode;
+    a.y = out.p;
+    a.yC = out.C;
+    a.yoff = out.off;
+    a.yf = yf;
+    const bool one = cin_pad == kKChunk;
+    if (mode == 2) {
+        // the output layer: at most 16 channels, in one group; the first four need one row block
+        if (one && a.W >= 16) return N <= 4 ? launch_rows<4, 1, 2, 2, 1>(n, a) : launch_rows<4, 1, 2, 2, 2>(n, a);
+        return N <= 4 ? launch_taps<4, 1, 1>(n, a) : launch_taps<4, 1, 2>(n, a);
+    }
+    const int groups = N / 32;
+    if ((one && a.W >= 16) || chunk_order(a.H, a.W)) {
+        const bool narrow = a.W <= 16;
+        // eight rows per wave where that still gives every SIMD two waves
+        const size_t waves8 = (size_t)a.P / 128 * groups;
+        const bool tall = waves8 >= 2048;
+        if (groups % 4 == 0) return tall ? launch_rows<8, 4, 1, 1, 2>(n, a) : launch_rows<4, 4, 1, 1, 2>(n, a);
+        if (groups % 2 == 0) {
+            if (narrow) return tall ? launch_rows<8, 2, 1, 2, 2>(n, a) : launch_rows<4, 2, 1, 2, 2>(n, a);
+            return tall ? launch_rows<8, 2, 2, 1, 2>(n, a) : launch_rows<4, 2, 2, 1, 2>(n, a);
+        }
+        return narrow ? launch_rows<4, 1, 1, 4, 2>(n, a) : launch_rows<4, 1, 2, 2, 2>(n, a);
+    }
+    if ((size_t)a.P / 64 * groups >= 2048) return launch_taps<4, 1, 2>(n, a);
+    return launch_taps<1, 1, 2>(n, a);
 }
 
 clbm_status prep_weights(clbm_net* n)
 {
+    PrepTable t;
+    std::memset(&t, 0, sizeof t);
+    t.layers = kLayers;
     for (int k = 0; k < kLayers; ++k) {
         const Layer& l = n->L[k];
-        const size_t nf = (size_t)l.nout_pad * 9 * l.cin_pad;
-        const size_t nbk = l.wb ? (size_t)l.cin_pad * 9 * l.cout_kpad : 0;
-        hipLaunchKernelGGL(k_weight_prep, grid1(std::max(nf, nbk)), dim3(256), 0, n->stream,
-                           n->params + l.woff, l.cout, l.cin, l.nout_pad, l.cin_pad, l.cout_kpad,
-                           l.wf, l.wb);
-        CLBM_HIP(hipGetLastError());
+        PrepLayer& p = t.l[k];
+        p.woff = l.woff;
+        p.wf = l.wf;
+        p.wb = l.wb;
+        p.cin = l.cin;
+        p.cout = l.cout;
+        p.chunks_f = l.cin_pad / kKChunk;
+        p.chunks_b = l.cout_kpad / kKChunk;
+        p.first = t.total;
+        p.lanes_f = l.cout_kpad / 32 * p.chunks_f * 9 * 128;
+        t.total += p.lanes_f * (l.wb ? 2 : 1);
     }
+    hipLaunchKernelGGL(k_weight_prep, grid1((size_t)t.total), dim3(256), 0, n->stream, n->params, t);
+    CLBM_HIP(hipGetLastError());
     n->weights_stale = 0;
     return CLBM_OK;
 }
@@ -1046,9 +848,7 @@ clbm_status conv_backward(clbm_net* n, int k, TView dz)
     CLBM_HIP(hipGetLastError());
     // input gradient: convolution of dz with the flipped, transposed kernel
     if (l.din.p) {
-        const int nb = (l.cin % 64 == 0) ? 4 : 2;
-        return conv_launch(n, l, dz, l.cout_kpad, l.wb, nullptr, l.cin, nb, round_up(l.cin, 16 * nb), 1,
-                           l.din, nullptr);
+        return conv_launch(n, l, dz, l.cout_kpad, l.wb, nullptr, l.cin, 1, l.din, nullptr);
     }
     return CLBM_OK;
 }
@@ -1171,8 +971,8 @@ clbm_status clbm_net_forward(clbm_net* n, const float* d_x, float* d_y)
     Layer* L = n->L;
     auto fwd = [&](int k) {
         const Layer& l = L[k];
-        return conv_launch(n, l, l.in, l.cin_pad, l.wf, n->params + l.boff, l.cout, l.nb, l.nout_pad,
-                           k == 14 ? 2 : 0, l.out, k == 14 ? n->yout : nullptr);
+        return conv_launch(n, l, l.in, l.cin_pad, l.wf, n->params + l.boff, l.cout, k == 14 ? 2 : 0, l.out,
+                           k == 14 ? n->yout : nullptr);
     };
     auto V = [](bf16* p, int C, int off) { return TView{p, C, off}; };
     if ((st = fwd(0)) || (st = fwd(1))) return st;
