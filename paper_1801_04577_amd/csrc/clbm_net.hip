@@ -29,195 +29,11 @@
 
 #include "clbm_conv.h"
 #include "clbm_host.h"
+#include "clbm_wgrad.h"
 
 namespace clbm {
 
 constexpr int kLayers = 15;
-
-// Weight gradient of one 3x3 convolution over a range of pixels (split-K):
-// part[s][co][tap][ci] = sum over the pixels p of split s of dz[p][co] * x[src(p,tap)][ci],
-// a GEMM whose reduction runs over pixels, the slow index of NHWC. A workgroup of three
-// waves owns a (16 NCO) co x (16 NCI) ci block and one split; wave w takes the three
-// taps of kernel row w. Per chunk of 32 pixels the workgroup stages dz and the nine
-// shifted input tiles in LDS channel-major (the 32 pixels of one channel contiguous, two
-// pixels per 32-bit write), so every MFMA operand - 8 consecutive pixels of one channel -
-// is one 16-byte LDS read: A = dz^T (co x pixels), B = shifted x (pixels x ci). Each wave
-// reads its NCO dz fragments once per chunk and issues 3 NCO NCI MFMAs. NCO and NCI
-// divide the padded channel counts (16-channel blocks), so the block has no padding.
-constexpr int kWgP = 32;          // pixels per chunk: the MFMA K
-constexpr int kWgLd = kWgP + 8;   // LDS row stride in elements (staggers the banks)
-constexpr int kWgThreads = 192;
-
-__device__ __forceinline__ unsigned bf16_bits(bf16 v) { return (unsigned)__builtin_bit_cast(unsigned short, v); }
-
-template <int NCO, int NCI>
-__global__ void __launch_bounds__(kWgThreads) k_wgrad(const bf16* __restrict__ dz, int zC, int Cout,
-                                                      const bf16* __restrict__ x, int xC, int xoff, int Cin,
-                                                      int H, int W, int P, int pix_per_split,
-                                                      float* __restrict__ part, float* __restrict__ bpart)
-{
-    constexpr int CO = 16 * NCO, CI = 16 * NCI;
-    __shared__ __attribute__((aligned(16))) bf16 sdz[CO * kWgLd];
-    __shared__ __attribute__((aligned(16))) bf16 sx[9][CI * kWgLd];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cib_n = Cin / CI;
-    const int co0 = (blockIdx.x / cib_n) * CO, ci0 = (blockIdx.x % cib_n) * CI;
-    const int split = blockIdx.y;
-    const int HW = H * W;
-    const int pbeg = split * pix_per_split, pend = min(P, pbeg + pix_per_split);
-    const int r16 = lane & 15, k8 = (lane >> 4) * 8;
-    // The workgroups of the first input-channel block also sum dz over their pixels: the
-    // bias gradient's partial for this split (bpart[split][co]), from the staged dz.
-    const bool bias = bpart != nullptr && blockIdx.x % cib_n == 0;
-    float bsum = 0.f;
-    f32x4 acc[3][NCO][NCI];
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int i = 0; i < NCO; ++i)
-#pragma unroll
-            for (int j = 0; j < NCI; ++j) acc[d][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bf16x8 zero = {};
-    // image, row and column of the chunk's first pixel, advanced with the chunk (no
-    // division per staged pixel)
-    int cb = pbeg / HW, cy = (pbeg - cb * HW) / W, cx = pbeg - cb * HW - cy * W;
-    for (int pk = pbeg; pk < pend; pk += kWgP) {
-        // stage dz: 16 pixel pairs x (2 NCO) channel octets
-        for (int t = tid; t < 16 * 2 * NCO; t += kWgThreads) {
-            const int pair = t / (2 * NCO), oct = t % (2 * NCO);
-            const int p = pk + 2 * pair, co = co0 + 8 * oct;
-            bf16x8 v0 = zero, v1 = zero;
-            if (p < pend) v0 = *reinterpret_cast<const bf16x8*>(dz + (size_t)p * zC + co);
-            if (p + 1 < pend) v1 = *reinterpret_cast<const bf16x8*>(dz + (size_t)(p + 1) * zC + co);
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                *reinterpret_cast<unsigned*>(&sdz[(8 * oct + c) * kWgLd + 2 * pair]) =
-                    bf16_bits(v0[c]) | (bf16_bits(v1[c]) << 16);
-        }
-        // stage the nine shifted input tiles: 9 taps x 16 pixel pairs x (2 NCI) channel octets
-#pragma unroll 2
-        for (int t = tid; t < 9 * 16 * 2 * NCI; t += kWgThreads) {
-            const int tap = t / (32 * NCI), rest = t % (32 * NCI);
-            const int pair = rest / (2 * NCI), oct = rest % (2 * NCI);
-            const int ci = ci0 + 8 * oct;
-            bf16x8 v[2] = {zero, zero};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int p = pk + 2 * pair + h;
-                if (p < pend) {
-                    int b = cb, py = cy, px = cx + 2 * pair + h;
-                    while (px >= W) {
-                        px -= W;
-                        if (++py == H) {
-                            py = 0;
-                            ++b;
-                        }
-                    }
-                    const int sy = py + tap / 3 - 1, sx2 = px + tap % 3 - 1;
-                    if (sy >= 0 && sy < H && sx2 >= 0 && sx2 < W)
-                        v[h] = *reinterpret_cast<const bf16x8*>(x + (size_t)(b * HW + sy * W + sx2) * xC + xoff + ci);
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                *reinterpret_cast<unsigned*>(&sx[tap][(8 * oct + c) * kWgLd + 2 * pair]) =
-                    bf16_bits(v[0][c]) | (bf16_bits(v[1][c]) << 16);
-        }
-        __syncthreads();
-        if (bias && tid < CO) {
-#pragma unroll 8
-            for (int q = 0; q < kWgP; ++q) bsum += bf2f(sdz[tid * kWgLd + q]);
-        }
-        bf16x8 a[NCO];
-#pragma unroll
-        for (int i = 0; i < NCO; ++i) a[i] = *reinterpret_cast<const bf16x8*>(&sdz[(16 * i + r16) * kWgLd + k8]);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const bf16* xt = sx[3 * wave + d];
-#pragma unroll
-            for (int j = 0; j < NCI; ++j) {
-                const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&xt[(16 * j + r16) * kWgLd + k8]);
-#pragma unroll
-                for (int i = 0; i < NCO; ++i)
-                    acc[d][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], bv, acc[d][i][j], 0, 0, 0);
-            }
-        }
-        __syncthreads();  // the next chunk overwrites the tiles
-        cx += kWgP;
-        while (cx >= W) {
-            cx -= W;
-            if (++cy == H) {
-                cy = 0;
-                ++cb;
-            }
-        }
-    }
-    // row of the result = output channel co0 + 16 i + 4 (lane / 16) + v, column = ci
-    float* out = part + (size_t)split * Cout * 9 * Cin + (size_t)(co0 + 4 * (lane >> 4)) * 9 * Cin + ci0 + r16;
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int i = 0; i < NCO; ++i)
-#pragma unroll
-            for (int j = 0; j < NCI; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    out[((size_t)(16 * i + v) * 9 + 3 * wave + d) * Cin + 16 * j] = acc[d][i][j][v];
-    if (bias && tid < CO) bpart[(size_t)split * Cout + co0 + tid] = bsum;
-}
-
-// Largest 16-channel block count in {4, 2, 1} that divides n16 (channels / 16).
-inline int wgrad_blocks16(int n16) { return n16 % 4 == 0 ? 4 : (n16 % 2 == 0 ? 2 : 1); }
-
-// Pixels per split of the weight gradient of a layer with P pixels and the given padded
-// channel counts: about 512 workgroups (two per CU), at most 256 splits, at least 8
-// chunks each.
-inline int wgrad_pixels_per_split(size_t P, int cout16, int cin_pad)
-{
-    const size_t blocks = (size_t)(cout16 / (16 * wgrad_blocks16(cout16 / 16))) *
-                          (cin_pad / (16 * wgrad_blocks16(cin_pad / 16)));
-    size_t splits = std::min<size_t>(256, std::max<size_t>(1, 512 / blocks));
-    splits = std::min(splits, std::max<size_t>(1, P / (8 * kWgP)));
-    const size_t pps = (P + splits - 1) / splits;
-    return (int)((pps + kWgP - 1) / kWgP * kWgP);
-}
-
-// Sum of the split partials in split order, written in the canonical layout
-// grad[co][ci][ky][kx] for co < Cout_real, ci < Cin_real (the partials use the padded
-// strides Cout, Cin). Threads run along the partials' own layout [co][tap][ci], so
-// the reads of each split are contiguous across a wave.
-__global__ void k_wgrad_reduce(const float* __restrict__ part, int splits, int Cout, int Cin,
-                               int Cout_real, int Cin_real, float* __restrict__ grad)
-{
-    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t plane = (size_t)Cout * 9 * Cin;
-    if (k >= plane) return;
-    const int co = (int)(k / (9 * (size_t)Cin)), r = (int)(k - (size_t)co * 9 * Cin);
-    const int tap = r / Cin, ci = r - tap * Cin;
-    if (co >= Cout_real || ci >= Cin_real) return;
-    float s = 0.f;
-#pragma unroll 8
-    for (int sp = 0; sp < splits; ++sp) s += part[sp * plane + k];
-    grad[((size_t)co * Cin_real + ci) * 9 + tap] = s;
-}
-
-// Sum of the bias partials of channel blockIdx.x: each thread sums a fixed strided
-// subset of the splits, then a fixed-order tree over the 256 threads.
-__global__ void __launch_bounds__(256) k_bias_reduce(const float* __restrict__ part, int splits, int C,
-                                                     float* __restrict__ g)
-{
-    __shared__ float lds[256];
-    const int c = blockIdx.x, t = threadIdx.x;
-    float s = 0.f;
-    for (int sp = t; sp < splits; sp += 256) s += part[(size_t)sp * C + c];
-    lds[t] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) lds[t] += lds[t + w];
-        __syncthreads();
-    }
-    if (t == 0) g[c] = lds[0];
-}
 
 // fp32 NCHW input planes -> bf16 NHWC with zero channel padding.
 __global__ void k_pack_input(const float* __restrict__ xin, int Cin, int HW, int P,
@@ -621,11 +437,10 @@ void layout_net(clbm_net* n, Alloc& a)
     size_t wp = 0, bp = 0;
     for (int k = 0; k < kLayers; ++k) {
         const Layer& l = n->L[k];
-        const size_t P = (size_t)B * l.H * l.W;
-        const int c16 = round_up(l.cout, 16);
-        const size_t pps = (size_t)wgrad_pixels_per_split(P, c16, l.cin_pad);
-        wp = std::max(wp, (P + pps - 1) / pps * c16 * 9 * l.cin_pad);
-        bp = std::max(bp, (P + pps - 1) / pps * c16);
+        const size_t P = (size_t)B * l.H * l.W, pixels = wgrad_pixels_per_split(P, l.cout, l.cin_pad);
+        const size_t splits = (P + pixels - 1) / pixels;
+        wp = std::max(wp, splits * l.cout_kpad * 9 * l.cin_pad);
+        bp = std::max(bp, splits * l.cout_kpad);
     }
     n->wpart_floats = wp;
     n->wpart = a.take<float>(wp);
@@ -815,37 +630,59 @@ clbm_status upsample(clbm_net* n, TView x, int C, int H, int W, TView y)
     return ew_launch_check();
 }
 
+template <int NA, int RING, bool WIDE>
+clbm_status wgrad_ring(clbm_net* n, const WgradArgs& g)
+{
+    const dim3 grid((g.splits + 7) / 8 * 8 * g.co_blocks * g.ci_blocks), block(192);
+    if (g.W % 32 == 0)
+        hipLaunchKernelGGL((k_wgrad<NA, RING, WIDE, true>), grid, block, 0, n->stream, g);
+    else
+        hipLaunchKernelGGL((k_wgrad<NA, RING, WIDE, false>), grid, block, 0, n->stream, g);
+    CLBM_HIP(hipGetLastError());
+    return CLBM_OK;
+}
+
+// Weight and bias gradients of a layer.
+template <int NA>
+clbm_status wgrad_launch(clbm_net* n, const Layer& l, TView dz)
+{
+    WgradArgs g;
+    g.dz = dz.p;
+    g.zC = dz.C;
+    g.x = l.in.p;
+    g.xC = l.in.C;
+    g.xoff = l.in.off;
+    g.H = l.H;
+    g.W = l.W;
+    g.P = n->d.batch * l.H * l.W;
+    g.co_blocks = l.cout_kpad / (16 * NA);
+    g.ci_blocks = l.cin_pad / 32;
+    g.pixels = wgrad_pixels_per_split((size_t)g.P, l.cout, l.cin_pad);
+    g.splits = (g.P + g.pixels - 1) / g.pixels;
+    g.part = n->wpart;
+    g.bpart = n->bpart;
+    // the ring holds two rows and two steps: rows of up to 159 pixels in 512
+    const int need = 2 * l.W + 2 + 2 * kWgStep;
+    const clbm_status st = need <= 256   ? wgrad_ring<NA, 256, false>(n, g)
+                           : need <= 512 ? wgrad_ring<NA, 512, false>(n, g)
+                                         : wgrad_ring<NA, 256, true>(n, g);
+    if (st != CLBM_OK) return st;
+    const size_t weights = (size_t)l.cout_kpad * 9 * l.cin_pad;
+    hipLaunchKernelGGL(k_wgrad_reduce<NA>, dim3((unsigned)(weights / 64 + (l.cout_kpad + 63) / 64)), dim3(64), 0,
+                       n->stream, n->wpart, n->bpart, g.splits, g.co_blocks, g.ci_blocks, l.cout, l.cin,
+                       n->grads + l.woff, n->grads + l.boff);
+    CLBM_HIP(hipGetLastError());
+    return CLBM_OK;
+}
+
 // Backward through one convolution: dz (gradient w.r.t. its output pre-activation,
 // ReLU already applied) -> weight and bias gradients, and the input gradient when the
 // layer has one.
 clbm_status conv_backward(clbm_net* n, int k, TView dz)
 {
     const Layer& l = n->L[k];
-    const int B = n->d.batch;
-    const int P = B * l.H * l.W;
-    const int cout16 = round_up(l.cout, 16);
-    const int pps = wgrad_pixels_per_split((size_t)P, cout16, l.cin_pad);
-    const int splits = (P + pps - 1) / pps;
-    // weight gradient
-    const int nco = wgrad_blocks16(cout16 / 16), nci = wgrad_blocks16(l.cin_pad / 16);
-    const void* wg = nco == 4 ? (nci == 4 ? (const void*)&k_wgrad<4, 4> : nci == 2 ? (const void*)&k_wgrad<4, 2> : (const void*)&k_wgrad<4, 1>)
-                   : nco == 2 ? (nci == 4 ? (const void*)&k_wgrad<2, 4> : nci == 2 ? (const void*)&k_wgrad<2, 2> : (const void*)&k_wgrad<2, 1>)
-                              : (nci == 4 ? (const void*)&k_wgrad<1, 4> : nci == 2 ? (const void*)&k_wgrad<1, 2> : (const void*)&k_wgrad<1, 1>);
-    {
-        const bf16* zp = dz.p; int zc = dz.C, co = cout16; const bf16* xp = l.in.p; int xc = l.in.C, xo = l.in.off;
-        int ci = l.cin_pad, h = l.H, w = l.W, pp = P, ps = pps; float* pt = n->wpart; float* bt = n->bpart;
-        void* args[] = {&zp, &zc, &co, &xp, &xc, &xo, &ci, &h, &w, &pp, &ps, &pt, &bt};
-        CLBM_HIP(hipLaunchKernel(wg, dim3((cout16 / (16 * nco)) * (l.cin_pad / (16 * nci)), splits),
-                                 dim3(kWgThreads), args, 0, n->stream));
-    }
-    CLBM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_wgrad_reduce, grid1((size_t)cout16 * 9 * l.cin_pad), dim3(256), 0, n->stream,
-                       n->wpart, splits, cout16, l.cin_pad, l.cout, l.cin, n->grads + l.woff);
-    CLBM_HIP(hipGetLastError());
-    // bias gradient: the weight-gradient kernel left one partial per split
-    hipLaunchKernelGGL(k_bias_reduce, dim3(l.cout), dim3(256), 0, n->stream, n->bpart, splits, cout16,
-                       n->grads + l.boff);
-    CLBM_HIP(hipGetLastError());
+    const clbm_status st = l.cout_kpad % 64 == 0 ? wgrad_launch<4>(n, l, dz) : wgrad_launch<2>(n, l, dz);
+    if (st != CLBM_OK) return st;
     // input gradient: convolution of dz with the flipped, transposed kernel
     if (l.din.p) {
         return conv_launch(n, l, dz, l.cout_kpad, l.wb, nullptr, l.cin, 1, l.din, nullptr);

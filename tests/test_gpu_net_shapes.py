@@ -1,0 +1,54 @@
+"""The network at grids and widths that select each convolution and weight-gradient kernel:
+rows shorter and longer than the kernels' tiles and rings, rows that are and are not a
+multiple of 32 pixels, images of a few pixels at the coarsest level, channel counts that
+are odd multiples of 32, and both widths of the output layer. Every output and gradient
+element against the reference network with BF16 storage of the operands, within the bound
+derived in test_gpu_net.py (4 x 2^-8 of the element and its tensor's largest)."""
+import numpy as np
+import pytest
+
+from oracle import net as ref
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # batch, height, width, cin, cout, widths
+    (16, 16, 16, 8, 3, (32, 64, 128, 256)),
+    (64, 24, 40, 8, 3, (32, 32, 64, 96)),
+    (2, 64, 160, 8, 3, (32, 64, 128, 256)),
+    (8, 16, 256, 3, 5, (64, 32, 96, 64)),
+    (32, 32, 16, 32, 16, (96, 64, 32, 160)),
+    (4, 32, 128, 9, 4, (64, 128, 64, 128)),
+]
+
+
+def worst(got, want):
+    """Largest deviation in units of 2^-8 (|want| + max |want|)."""
+    return float((np.abs(got - want) / np.maximum(2.0 ** -8 * (np.abs(want) + np.abs(want).max()), 1e-300)).max())
+
+
+@pytest.mark.parametrize("B,H,W,cin,cout,widths", CASES)
+def test_shapes_elementwise(B, H, W, cin, cout, widths):
+    import torch
+    import paper_1801_04577_amd as clbm
+    rng = np.random.default_rng(B + H + W)
+    params = [(w.astype(np.float32).astype(np.float64),
+               rng.normal(scale=0.05, size=b.shape).astype(np.float32).astype(np.float64))
+              for w, b in ref.init_params(cin, cout, widths, seed=3)]
+    xs = rng.normal(size=(B, cin, H, W)).astype(np.float32)
+    ts = rng.normal(scale=0.5, size=(B, cout, H, W)).astype(np.float32)
+    n = clbm.Net(B, H, W, cin, cout, widths)
+    n.set_params(torch.from_numpy(np.concatenate([np.concatenate([w.reshape(-1), b]) for w, b in params])
+                                  .astype(np.float32)))
+    y = n.forward(torch.from_numpy(xs)).cpu().numpy().astype(np.float64)
+    loss = n.backward(torch.from_numpy(ts))
+    grads = n.grads().cpu().numpy().astype(np.float64)
+    want_y = np.stack([ref.forward(params, x.astype(np.float64), quant=True) for x in xs])
+    want_loss, want = ref.loss_and_grads(params, xs.astype(np.float64), ts.astype(np.float64), quant=True)
+    ratios, k = [worst(y, want_y)], 0
+    for ww, wb in want:
+        for t in (ww, wb):
+            ratios.append(worst(grads[k:k + t.size].reshape(t.shape), t))
+            k += t.size
+    print("worst %.3f of the unit" % max(ratios), flush=True)
+    assert loss == pytest.approx(want_loss, rel=1e-3)
+    assert max(ratios) <= 4.0
