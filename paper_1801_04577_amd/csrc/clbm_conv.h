@@ -33,10 +33,13 @@ __device__ __forceinline__ bf16 f2bf(float v) { return (bf16)v; }
 struct ConvArgs {
     const bf16* x;       // input, NHWC
     int xC, xoff, Cin;   // channel stride and offset; input channels, a multiple of 32
+    int octs;            // octets of channels that are stored, when fewer than Cin (one chunk; the others are zero)
     const bf16* w;
     const float* bias;
     int N, H, W, P;      // output channels, image, pixels in all
     int mode;            // 0: relu(acc + bias) as bf16; 1: acc as bf16 (input gradients); 2: acc + bias, FP32 NCHW
+    const bf16* mask;    // mode 1: nullptr, or activations at the output's pixels: zero where not positive (ReLU)
+    int maskC;
     bf16* y;
     int yC, yoff;
     float* yf;
@@ -44,8 +47,15 @@ struct ConvArgs {
 
 // Epilogue of one pixel: lane group g = lane / 16 holds channels n0 + 8 g .. + 7.
 template <int NH>
-__device__ __forceinline__ void conv_store(const ConvArgs& a, const f32x4 (&acc)[NH], int n, size_t p, int img,
-                                           int rem)
+__device__ __forceinline__ void conv_bias(const ConvArgs& a, int n, float (&bias)[4 * NH])
+{
+#pragma unroll
+    for (int k = 0; k < 4 * NH; ++k) bias[k] = a.mode != 1 && n + k < a.N ? a.bias[n + k] : 0.f;
+}
+
+template <int NH>
+__device__ __forceinline__ void conv_store(const ConvArgs& a, const f32x4 (&acc)[NH], const float (&bias)[4 * NH],
+                                           int n, size_t p, int img, int rem)
 {
     if (a.mode == 2) {
 #pragma unroll
@@ -53,7 +63,7 @@ __device__ __forceinline__ void conv_store(const ConvArgs& a, const f32x4 (&acc)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int c = n + 4 * h + v;
-                if (c < a.N) a.yf[((size_t)img * a.N + c) * ((size_t)a.H * a.W) + rem] = acc[h][v] + a.bias[c];
+                if (c < a.N) a.yf[((size_t)img * a.N + c) * ((size_t)a.H * a.W) + rem] = acc[h][v] + bias[4 * h + v];
             }
         return;
     }
@@ -64,9 +74,15 @@ __device__ __forceinline__ void conv_store(const ConvArgs& a, const f32x4 (&acc)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 float r = acc[h][v];
-                if (a.mode == 0) r = fmaxf(r + a.bias[n + 4 * h + v], 0.f);
+                if (a.mode == 0) r = fmaxf(r + bias[4 * h + v], 0.f);
                 o[4 * h + v] = f2bf(r);
             }
+        if (a.mask) {
+            const bf16x8 m = *reinterpret_cast<const bf16x8*>(a.mask + p * a.maskC + n);
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (!(bf2f(m[k]) > 0.f)) o[k] = (bf16)0.f;
+        }
         *reinterpret_cast<bf16x8*>(a.y + p * a.yC + a.yoff + n) = o;
     }
 }
@@ -83,12 +99,12 @@ __device__ __forceinline__ void conv_store(const ConvArgs& a, const f32x4 (&acc)
 // its weights replaced tap row by tap row while the current chunk is multiplied.
 // LDS: [pixel][32 channels], the four 16-byte octets of a pixel rotated by its column so
 // that 16 neighbouring pixels cover all banks.
-template <int R, int CW, int PX, int PY, int NH>
+template <int R, int CW, int PX, int PY, int NH, bool ONE>
 __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs a)
 {
     constexpr int NT = 64 * CW * PX * PY, HX = 16 * PX + 2, HY = R * PY + 2, NPIX = HX * HY;
     constexpr int NA = (NPIX * 4 + NT - 1) / NT;
-    __shared__ __attribute__((aligned(16))) bf16 sa[2][NPIX * kKChunk];
+    __shared__ __attribute__((aligned(16))) bf16 sa[ONE ? 1 : 2][NPIX * kKChunk];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cw = wave % CW, wx = (wave / CW) % PX, wy = wave / (CW * PX);
@@ -96,7 +112,7 @@ __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs 
     const int bx = blockIdx.x % nbx, by = (blockIdx.x / nbx) % nby, img = blockIdx.x / (nbx * nby);
     const int x0 = bx * 16 * PX, y0 = by * R * PY;
     const int r16 = lane & 15, g = lane >> 4;
-    const int nch = a.Cin / kKChunk;
+    const int nch = ONE ? 1 : a.Cin / kKChunk;
     // the pixels this thread stages (octet tid % 4 of each; -1: outside the image, zero)
     const bf16* xi = a.x + (size_t)img * a.H * a.W * a.xC + a.xoff + 8 * (tid & 3);
     int so[NA];
@@ -105,7 +121,7 @@ __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs 
     for (int i = 0; i < NA; ++i) {
         const int t = tid + NT * i, px = t >> 2, oct = t & 3;
         const int hy = px / HX, hx = px - hy * HX, sy = y0 + hy - 1, sx = x0 + hx - 1;
-        so[i] = t < NPIX * 4 && sy >= 0 && sy < a.H && sx >= 0 && sx < a.W ? sy * a.W + sx : -1;
+        so[i] = t < NPIX * 4 && oct < a.octs && sy >= 0 && sy < a.H && sx >= 0 && sx < a.W ? sy * a.W + sx : -1;
         dst[i] = t < NPIX * 4 ? (unsigned)(px * kKChunk + ((oct ^ ((hx >> 2) & 3)) << 3)) : ~0u;
     }
     const bf16x8 zero = {};
@@ -145,11 +161,14 @@ __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs 
     fetch(0);
 #pragma unroll
     for (int dy = 0; dy < 3; ++dy) weights(0, dy);
+    const int n0 = (blockIdx.y * CW + cw) * 32 + 8 * g;
+    float bias[4 * NH];
+    if (ONE) conv_bias<NH>(a, n0, bias);   // with more chunks the registers are worth more than the wait
     put(0);
     __syncthreads();
     for (int c = 0; c < nch; ++c) {
-        const bool more = c + 1 < nch;
-        const bf16* s = sa[c & 1];
+        const bool more = !ONE && c + 1 < nch;
+        const bf16* s = sa[ONE ? 0 : c & 1];
         if (more) fetch(c + 1);
 #pragma unroll
         for (int r = 0; r < R + 2; ++r) {
@@ -176,11 +195,12 @@ __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs 
     }
     const int xx = x0 + wx * 16 + r16;
     if (xx >= a.W) return;
+    if (!ONE) conv_bias<NH>(a, n0, bias);
 #pragma unroll
     for (int o = 0; o < R; ++o) {
         const int yy = y0 + wy * R + o, rem = yy * a.W + xx;
         if (yy < a.H)
-            conv_store<NH>(a, acc[o], (blockIdx.y * CW + cw) * 32 + 8 * g, (size_t)img * a.H * a.W + rem, img, rem);
+            conv_store<NH>(a, acc[o], bias, n0, (size_t)img * a.H * a.W + rem, img, rem);
     }
 }
 
@@ -210,7 +230,7 @@ __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
         const int img = p / HW, rem = p - img * HW;
         py[j] = rem / a.W;
         px[j] = rem - py[j] * a.W;
-        xb[j] = a.x + (size_t)p * a.xC + a.xoff + 8 * g;
+        xb[j] = a.x + (size_t)p * a.xC + a.xoff + (g < a.octs ? 8 * g : 0);
     }
     const bf16x8 zero = {};
     const bf16* wp = a.w + (size_t)ng * NG * nch * kChunkW + lane * 8;
@@ -221,7 +241,7 @@ __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
         const int dy = lt / 3 - 1, dx = lt % 3 - 1;
 #pragma unroll
         for (int j = 0; j < MP; ++j) {
-            in[d][j] = (unsigned)(py[j] + dy) < (unsigned)a.H && (unsigned)(px[j] + dx) < (unsigned)a.W;
+            in[d][j] = g < a.octs && (unsigned)(py[j] + dy) < (unsigned)a.H && (unsigned)(px[j] + dx) < (unsigned)a.W;
             // a source outside the image is replaced by the pixel itself and not used
             const int off = in[d][j] ? (dy * a.W + dx) * a.xC : 0;
             va[d][j] = *reinterpret_cast<const bf16x8*>(xb[j] + off + lc * kKChunk);
@@ -247,6 +267,9 @@ __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
 #pragma unroll
     for (int d = 0; d < D; ++d)
         if (d < steps) load(d);
+    float bias[NG][4 * NH];
+#pragma unroll
+    for (int n = 0; n < NG; ++n) conv_bias<NH>(a, (ng * NG + n) * 32 + 8 * g, bias[n]);
     for (int s = 0; s < steps; s += D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -271,7 +294,7 @@ __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
 #pragma unroll
         for (int n = 0; n < NG; ++n)
             if ((ng * NG + n) * 32 < a.N)
-                conv_store<NH>(a, acc[j][n], (ng * NG + n) * 32 + 8 * g, (size_t)p, img, p - img * HW);
+                conv_store<NH>(a, acc[j][n], bias[n], (ng * NG + n) * 32 + 8 * g, (size_t)p, img, p - img * HW);
     }
 }
 

@@ -35,15 +35,18 @@ namespace clbm {
 
 constexpr int kLayers = 15;
 
-// fp32 NCHW input planes -> bf16 NHWC with zero channel padding.
-__global__ void k_pack_input(const float* __restrict__ xin, int Cin, int HW, int P,
-                             bf16* __restrict__ x, int xC)
+// fp32 NCHW input planes -> bf16 NHWC, channels padded to whole octets with zeros. A thread
+// writes one octet of one pixel; neighbouring threads read neighbouring pixels of a plane.
+__global__ void __launch_bounds__(256) k_pack_input(const float* __restrict__ xin, int Cin, int HW, int P,
+                                                    bf16* __restrict__ x, int xC)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= P * xC) return;
-    const int p = k / xC, c = k - p * xC;
+    const int p = blockIdx.x * 256 + threadIdx.x, c0 = blockIdx.y * 8;
+    if (p >= P) return;
     const int b = p / HW, r = p - b * HW;
-    x[k] = f2bf(c < Cin ? xin[((size_t)b * Cin + c) * HW + r] : 0.f);
+    bf16x8 o;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) o[c] = f2bf(c0 + c < Cin ? xin[((size_t)b * Cin + c0 + c) * HW + r] : 0.f);
+    *reinterpret_cast<bf16x8*>(x + (size_t)p * xC + c0) = o;
 }
 
 // Elementwise kernels over NHWC channel views. Each thread handles V consecutive
@@ -111,10 +114,11 @@ __global__ void k_upsample(const bf16* __restrict__ x, int xC, int xoff, int C, 
     else dst[0] = src[0];
 }
 
-// Gradient of the nearest upsampling: 2x2 sums (dy is 2H x 2W, dx is H x W).
+// Gradient through the nearest upsampling and the ReLU before it: 2x2 sums (dy is 2H x 2W,
+// dz is H x W), zero where the activation a is not positive.
 template <int V>
 __global__ void k_upsample_bwd(const bf16* __restrict__ dy, int dyC, int dyoff, int C, int H, int W,
-                               int B, bf16* __restrict__ dx, int dxC, int dxoff)
+                               int B, const bf16* __restrict__ a, int aC, bf16* __restrict__ dz, int zC)
 {
     const int Wi = 2 * W, CV = C / V;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -122,19 +126,18 @@ __global__ void k_upsample_bwd(const bf16* __restrict__ dy, int dyC, int dyoff, 
     const int c = (k % CV) * V, p = k / CV;
     const int b = p / (H * W), r = p - b * H * W, oy = r / W, ox = r - oy * W;
     const size_t base = (size_t)b * 4 * H * W;
-    float v00[V], v01[V], v10[V], v11[V], out[V];
+    float v00[V], v01[V], v10[V], v11[V], av[V], out[V];
+    load_v<V>(a + (size_t)p * aC + c, av);
     load_v<V>(dy + (base + (2 * oy) * Wi + 2 * ox) * dyC + dyoff + c, v00);
     load_v<V>(dy + (base + (2 * oy) * Wi + 2 * ox + 1) * dyC + dyoff + c, v01);
     load_v<V>(dy + (base + (2 * oy + 1) * Wi + 2 * ox) * dyC + dyoff + c, v10);
     load_v<V>(dy + (base + (2 * oy + 1) * Wi + 2 * ox + 1) * dyC + dyoff + c, v11);
 #pragma unroll
-    for (int i = 0; i < V; ++i) out[i] = v00[i] + v01[i] + v10[i] + v11[i];
-    store_v<V>(dx + (size_t)p * dxC + dxoff + c, out);
+    for (int i = 0; i < V; ++i) out[i] = av[i] > 0.f ? v00[i] + v01[i] + v10[i] + v11[i] : 0.f;
+    store_v<V>(dz + (size_t)p * zC + c, out);
 }
 
 // dz = (dskip + pool_backward(dpool)) * (a > 0), all at H x W; dpool is H/2 x W/2.
-// With dskip == nullptr and dpool == nullptr it is the plain ReLU gradient dz = dy * (a > 0)
-// where dy is passed as dskip.
 template <int V>
 __global__ void k_relu_grad(const bf16* __restrict__ dskip, int sC, int soff,
                             const bf16* __restrict__ dpool, int pC, const bf16* __restrict__ a,
@@ -145,66 +148,70 @@ __global__ void k_relu_grad(const bf16* __restrict__ dskip, int sC, int soff,
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= B * H * W * CV) return;
     const int c = (k % CV) * V, p = k / CV;
-    float g[V], av[V], out[V];
+    const int b = p / (H * W), r = p - b * H * W, py = r / W, px = r - py * W;
+    const int Wo = W / 2;
+    float g[V], d[V], av[V], out[V];
+    load_v<V>(dskip + (size_t)p * sC + soff + c, g);
+    load_v<V>(dpool + ((size_t)b * (H / 2) * Wo + (py / 2) * Wo + px / 2) * pC + c, d);
 #pragma unroll
-    for (int i = 0; i < V; ++i) g[i] = 0.f;
-    if (dskip) load_v<V>(dskip + (size_t)p * sC + soff + c, g);
-    if (dpool) {
-        const int b = p / (H * W), r = p - b * H * W, py = r / W, px = r - py * W;
-        const int Wo = W / 2;
-        float d[V];
-        load_v<V>(dpool + ((size_t)b * (H / 2) * Wo + (py / 2) * Wo + px / 2) * pC + c, d);
-#pragma unroll
-        for (int i = 0; i < V; ++i) g[i] += 0.25f * d[i];
-    }
+    for (int i = 0; i < V; ++i) g[i] += 0.25f * d[i];
     load_v<V>(a + (size_t)p * aC + aoff + c, av);
 #pragma unroll
     for (int i = 0; i < V; ++i) out[i] = av[i] > 0.f ? g[i] : 0.f;
     store_v<V>(dz + (size_t)p * zC + c, out);
 }
 
-// Mean squared error: dy = 2 (y - t)/n into a bf16 NHWC buffer (zero channel padding),
-// per-block sums of (y - t)^2 in FP64.
+// Mean squared error: dy = 2 (y - t)/n into a bf16 NHWC buffer (channels padded to whole
+// octets with zeros), per-block sums of (y - t)^2 in FP64. A thread takes whole pixels, so
+// the planes are read along their rows and an octet is one store; at most kMseBlocks partial
+// sums are left, in a fixed order (one block per 256 elements left 65 536 for one workgroup
+// to add: 56 + 65 us at batch 32 on 128^2, now 8.5 + 4.7).
+constexpr int kMseBlocks = 1024;
+
+__device__ __forceinline__ double block_sum_256(double s, double* lds)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
+    __syncthreads();
+    return (lds[0] + lds[1]) + (lds[2] + lds[3]);
+}
+
 __global__ void __launch_bounds__(256) k_mse(const float* __restrict__ yv, const float* __restrict__ t,
                                              int Cout, int HW, int P, int zC, double inv_n,
                                              bf16* __restrict__ dz, double* __restrict__ part)
 {
-    __shared__ double lds[256];
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ double lds[4];
     double s = 0.0;
-    if (k < P * zC) {
-        const int p = k / zC, c = k - p * zC;
-        float g = 0.f;
-        if (c < Cout) {
-            const int b = p / HW, r = p - b * HW;
-            const size_t i = ((size_t)b * Cout + c) * HW + r;
-            const double d = (double)yv[i] - (double)t[i];
-            s = d * d;
-            g = (float)(2.0 * d * inv_n);
+    for (int p = blockIdx.x * 256 + threadIdx.x; p < P; p += gridDim.x * 256) {
+        const int b = p / HW, r = p - b * HW;
+        for (int c0 = 0; c0 < zC; c0 += 8) {
+            bf16x8 o;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                float g = 0.f;
+                if (c0 + c < Cout) {
+                    const size_t i = ((size_t)b * Cout + c0 + c) * HW + r;
+                    const double d = (double)yv[i] - (double)t[i];
+                    s += d * d;
+                    g = (float)(2.0 * d * inv_n);
+                }
+                o[c] = f2bf(g);
+            }
+            *reinterpret_cast<bf16x8*>(dz + (size_t)p * zC + c0) = o;
         }
-        dz[k] = f2bf(g);
     }
-    lds[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) lds[threadIdx.x] += lds[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = lds[0];
+    s = block_sum_256(s, lds);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-__global__ void k_sum_d(const double* __restrict__ part, int n, double* __restrict__ out)
+__global__ void __launch_bounds__(256) k_sum_d(const double* __restrict__ part, int n, double* __restrict__ out)
 {
-    __shared__ double lds[256];
+    __shared__ double lds[4];
     double s = 0.0;
-    for (int k = threadIdx.x; k < n; k += blockDim.x) s += part[k];
-    lds[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) lds[threadIdx.x] += lds[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = lds[0];
+    for (int k = threadIdx.x; k < n; k += 256) s += part[k];
+    s = block_sum_256(s, lds);
+    if (threadIdx.x == 0) *out = s;
 }
 
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -317,9 +324,9 @@ struct clbm_net {
     float* bpart;      // bias-gradient partials
     double* lpart;     // loss partials
     double* loss;
-    bf16* xin;         // packed input (cin padded)
+    bf16* xin;         // packed input (cin padded to whole octets)
     float* yout;       // network output fp32 NCHW
-    bf16* dyout;       // loss gradient (cout padded to 32)
+    bf16* dyout;       // loss gradient (cout padded to whole octets)
     // activations
     bf16 *a1, *cat1, *p1, *a2, *cat2, *p2, *a3, *cat3, *p3, *a4, *m4, *d3a, *d3b, *d2a, *d2b, *d1a, *d1b;
     // activation gradients
@@ -364,8 +371,8 @@ void layout_net(clbm_net* n, Alloc& a)
     const int B = d.batch, H = d.height, W = d.width;
     const int w1 = d.widths[0], w2 = d.widths[1], w3 = d.widths[2], w4 = d.widths[3];
     const size_t P1 = (size_t)B * H * W, P2 = P1 / 4, P3 = P1 / 16, P4 = P1 / 64;
-    const int cinp = round_up(d.cin, 32);
-    // activations
+    const int cinp = round_up(d.cin, 8), coutp = round_up(d.cout, 8);
+    // activations (input and output gradient hold whole octets of channels)
     n->xin = a.take<bf16>(P1 * cinp);
     n->a1 = a.take<bf16>(P1 * w1);
     n->cat1 = a.take<bf16>(P1 * (w2 + w1));
@@ -385,7 +392,7 @@ void layout_net(clbm_net* n, Alloc& a)
     n->d1a = a.take<bf16>(P1 * w1);
     n->d1b = a.take<bf16>(P1 * w1);
     n->yout = a.take<float>(P1 * d.cout);
-    n->dyout = a.take<bf16>(P1 * 32);
+    n->dyout = a.take<bf16>(P1 * coutp);
     // gradients
     n->g_d1b = a.take<bf16>(P1 * w1);
     n->g_d1a = a.take<bf16>(P1 * w1);
@@ -445,7 +452,7 @@ void layout_net(clbm_net* n, Alloc& a)
     n->wpart_floats = wp;
     n->wpart = a.take<float>(wp);
     n->bpart = a.take<float>(bp);
-    n->lpart = a.take<double>((P1 * 32 + 255) / 256);
+    n->lpart = a.take<double>(kMseBlocks);
     n->loss = a.take<double>(1);
 
     // views: forward input/output of each layer
@@ -494,16 +501,17 @@ bool vec8(std::initializer_list<int> v)
     return true;
 }
 
-// Gradient of the nearest upsampling into a channel view (dy: 2H x 2W, dx: H x W).
-clbm_status upsample_bwd(clbm_net* n, TView dy, int C, int H, int W, TView dx)
+// Gradient of a decoder level's upsampling (the first C channels of dy, 2H x 2W) through the
+// ReLU of the activations act (H x W).
+clbm_status upsample_bwd(clbm_net* n, TView dy, int C, int H, int W, TView act, TView dz)
 {
     const int B = n->d.batch;
-    if (vec8({C, dy.C, dy.off, dx.C, dx.off}))
+    if (vec8({C, dy.C, dy.off, act.C, dz.C}))
         hipLaunchKernelGGL(k_upsample_bwd<8>, grid1((size_t)B * H * W * (C / 8)), dim3(256), 0, n->stream,
-                           dy.p, dy.C, dy.off, C, H, W, B, dx.p, dx.C, dx.off);
+                           dy.p, dy.C, dy.off, C, H, W, B, act.p, act.C, dz.p, dz.C);
     else
         hipLaunchKernelGGL(k_upsample_bwd<1>, grid1((size_t)B * H * W * C), dim3(256), 0, n->stream,
-                           dy.p, dy.C, dy.off, C, H, W, B, dx.p, dx.C, dx.off);
+                           dy.p, dy.C, dy.off, C, H, W, B, act.p, act.C, dz.p, dz.C);
     CLBM_HIP(hipGetLastError());
     return CLBM_OK;
 }
@@ -513,8 +521,9 @@ clbm_status launch_rows(clbm_net* n, const ConvArgs& a)
 {
     const int B = a.P / (a.H * a.W);
     const size_t blocks = (size_t)((a.W + 16 * PX - 1) / (16 * PX)) * ((a.H + R * PY - 1) / (R * PY)) * B;
-    hipLaunchKernelGGL((k_conv_rows<R, CW, PX, PY, NH>), dim3((unsigned)blocks, (a.N + 32 * CW - 1) / (32 * CW)),
-                       dim3(64 * CW * PX * PY), 0, n->stream, a);
+    const dim3 grid((unsigned)blocks, (a.N + 32 * CW - 1) / (32 * CW)), block(64 * CW * PX * PY);
+    if (a.Cin == kKChunk) hipLaunchKernelGGL((k_conv_rows<R, CW, PX, PY, NH, true>), grid, block, 0, n->stream, a);
+    else hipLaunchKernelGGL((k_conv_rows<R, CW, PX, PY, NH, false>), grid, block, 0, n->stream, a);
     CLBM_HIP(hipGetLastError());
     return CLBM_OK;
 }
@@ -538,13 +547,14 @@ bool chunk_order(int H, int W)
 }
 
 clbm_status conv_launch(clbm_net* n, const Layer& l, TView in, int cin_pad, const bf16* w,
-                        const float* bias, int N, int mode, TView out, float* yf)
+                        const float* bias, int N, int mode, TView out, float* yf, TView mask = TView{nullptr, 0, 0})
 {
     ConvArgs a;
     a.x = in.p;
     a.xC = in.C;
     a.xoff = in.off;
     a.Cin = cin_pad;
+    a.octs = in.C < cin_pad ? in.C / 8 : cin_pad / 8;
     a.w = w;
     a.bias = bias;
     a.N = N;
@@ -556,6 +566,8 @@ clbm_status conv_launch(clbm_net* n, const Layer& l, TView in, int cin_pad, cons
     a.yC = out.C;
     a.yoff = out.off;
     a.yf = yf;
+    a.mask = mask.p ? mask.p + mask.off : nullptr;
+    a.maskC = mask.C;
     const bool one = cin_pad == kKChunk;
     if (mode == 2) {
         // the output layer: at most 16 channels, in one group; the first four need one row block
@@ -652,6 +664,8 @@ clbm_status wgrad_launch(clbm_net* n, const Layer& l, TView dz)
     g.x = l.in.p;
     g.xC = l.in.C;
     g.xoff = l.in.off;
+    g.zocts = dz.C < l.cout_kpad ? dz.C / 8 : l.cout_kpad / 8;
+    g.xocts = l.in.C < l.cin_pad ? l.in.C / 8 : l.cin_pad / 8;
     g.H = l.H;
     g.W = l.W;
     g.P = n->d.batch * l.H * l.W;
@@ -677,15 +691,15 @@ clbm_status wgrad_launch(clbm_net* n, const Layer& l, TView dz)
 
 // Backward through one convolution: dz (gradient w.r.t. its output pre-activation,
 // ReLU already applied) -> weight and bias gradients, and the input gradient when the
-// layer has one.
-clbm_status conv_backward(clbm_net* n, int k, TView dz)
+// layer has one, taken through the ReLU of the activations `mask` where that is given.
+clbm_status conv_backward(clbm_net* n, int k, TView dz, TView mask = TView{nullptr, 0, 0})
 {
     const Layer& l = n->L[k];
     const clbm_status st = l.cout_kpad % 64 == 0 ? wgrad_launch<4>(n, l, dz) : wgrad_launch<2>(n, l, dz);
     if (st != CLBM_OK) return st;
     // input gradient: convolution of dz with the flipped, transposed kernel
     if (l.din.p) {
-        return conv_launch(n, l, dz, l.cout_kpad, l.wb, nullptr, l.cin, 1, l.din, nullptr);
+        return conv_launch(n, l, dz, l.cout_kpad, l.wb, nullptr, l.cin, 1, l.din, nullptr, mask);
     }
     return CLBM_OK;
 }
@@ -801,8 +815,8 @@ clbm_status clbm_net_forward(clbm_net* n, const float* d_x, float* d_y)
     const int w1 = d.widths[0], w2 = d.widths[1], w3 = d.widths[2], w4 = d.widths[3];
     clbm_status st = CLBM_OK;
     if (n->weights_stale && (st = prep_weights(n)) != CLBM_OK) return st;
-    const int cinp = round_up(d.cin, 32);
-    hipLaunchKernelGGL(k_pack_input, grid1((size_t)B * H * W * cinp), dim3(256), 0, n->stream, d_x, d.cin,
+    const int cinp = round_up(d.cin, 8);
+    hipLaunchKernelGGL(k_pack_input, dim3((B * H * W + 255) / 256, cinp / 8), dim3(256), 0, n->stream, d_x, d.cin,
                        H * W, B * H * W, n->xin, cinp);
     CLBM_HIP(hipGetLastError());
     Layer* L = n->L;
@@ -839,58 +853,47 @@ clbm_status clbm_net_backward(clbm_net* n, const float* d_target, double* loss)
     const int w1 = d.widths[0], w2 = d.widths[1], w3 = d.widths[2], w4 = d.widths[3];
     const int P1 = B * H * W;
     auto V = [](bf16* p, int C, int off) { return TView{p, C, off}; };
-    const TView none = V(nullptr, 0, 0);
     clbm_status st = CLBM_OK;
     // loss and its gradient
-    const int nblk = (P1 * 32 + 255) / 256;
-    hipLaunchKernelGGL(k_mse, dim3(nblk), dim3(256), 0, n->stream, n->yout, d_target, d.cout, H * W, P1,
-                       32, 1.0 / ((double)P1 * d.cout), n->dyout, n->lpart);
+    const int nblk = std::min((P1 + 255) / 256, kMseBlocks), coutp = round_up(d.cout, 8);
+    hipLaunchKernelGGL(k_mse, dim3(nblk), dim3(256), 0, n->stream, n->yout, d_target, d.cout, H * W, P1, coutp,
+                       1.0 / ((double)P1 * d.cout), n->dyout, n->lpart);
     CLBM_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_sum_d, dim3(1), dim3(256), 0, n->stream, n->lpart, nblk, n->loss);
     CLBM_HIP(hipGetLastError());
     auto zv = [&](int C) { return TView{n->g_z, C, 0}; };
-    // output layer (no activation)
-    if ((st = conv_backward(n, 14, V(n->dyout, 32, 0)))) return st;
+    // output layer (no activation); each input gradient leaves its convolution as the gradient
+    // before the ReLU of the layer below
+    if ((st = conv_backward(n, 14, V(n->dyout, coutp, 0), V(n->d1b, w1, 0)))) return st;
     // level-1 decoder
-    if ((st = relu_grad(n, V(n->g_d1b, w1, 0), none, V(n->d1b, w1, 0), w1, H, W, zv(w1)))) return st;
-    if ((st = conv_backward(n, 13, zv(w1)))) return st;
-    if ((st = relu_grad(n, V(n->g_d1a, w1, 0), none, V(n->d1a, w1, 0), w1, H, W, zv(w1)))) return st;
-    if ((st = conv_backward(n, 12, zv(w1)))) return st;
+    if ((st = conv_backward(n, 13, V(n->g_d1b, w1, 0), V(n->d1a, w1, 0)))) return st;
+    if ((st = conv_backward(n, 12, V(n->g_d1a, w1, 0)))) return st;
     // g_cat1 = [d up(d2b) | d s1]
-    if ((st = upsample_bwd(n, V(n->g_cat1, w2 + w1, 0), w2, H / 2, W / 2, V(n->g_d2b, w2, 0)))) return st;
+    if ((st = upsample_bwd(n, V(n->g_cat1, w2 + w1, 0), w2, H / 2, W / 2, V(n->d2b, w2, 0), V(n->g_d2b, w2, 0)))) return st;
     // level-2 decoder
-    if ((st = relu_grad(n, V(n->g_d2b, w2, 0), none, V(n->d2b, w2, 0), w2, H / 2, W / 2, zv(w2)))) return st;
-    if ((st = conv_backward(n, 11, zv(w2)))) return st;
-    if ((st = relu_grad(n, V(n->g_d2a, w2, 0), none, V(n->d2a, w2, 0), w2, H / 2, W / 2, zv(w2)))) return st;
-    if ((st = conv_backward(n, 10, zv(w2)))) return st;
-    if ((st = upsample_bwd(n, V(n->g_cat2, w3 + w2, 0), w3, H / 4, W / 4, V(n->g_d3b, w3, 0)))) return st;
+    if ((st = conv_backward(n, 11, V(n->g_d2b, w2, 0), V(n->d2a, w2, 0)))) return st;
+    if ((st = conv_backward(n, 10, V(n->g_d2a, w2, 0)))) return st;
+    if ((st = upsample_bwd(n, V(n->g_cat2, w3 + w2, 0), w3, H / 4, W / 4, V(n->d3b, w3, 0), V(n->g_d3b, w3, 0)))) return st;
     // level-3 decoder
-    if ((st = relu_grad(n, V(n->g_d3b, w3, 0), none, V(n->d3b, w3, 0), w3, H / 4, W / 4, zv(w3)))) return st;
-    if ((st = conv_backward(n, 9, zv(w3)))) return st;
-    if ((st = relu_grad(n, V(n->g_d3a, w3, 0), none, V(n->d3a, w3, 0), w3, H / 4, W / 4, zv(w3)))) return st;
-    if ((st = conv_backward(n, 8, zv(w3)))) return st;
-    if ((st = upsample_bwd(n, V(n->g_cat3, w4 + w3, 0), w4, H / 8, W / 8, V(n->g_m4, w4, 0)))) return st;
+    if ((st = conv_backward(n, 9, V(n->g_d3b, w3, 0), V(n->d3a, w3, 0)))) return st;
+    if ((st = conv_backward(n, 8, V(n->g_d3a, w3, 0)))) return st;
+    if ((st = upsample_bwd(n, V(n->g_cat3, w4 + w3, 0), w4, H / 8, W / 8, V(n->m4, w4, 0), V(n->g_m4, w4, 0)))) return st;
     // bottom level
-    if ((st = relu_grad(n, V(n->g_m4, w4, 0), none, V(n->m4, w4, 0), w4, H / 8, W / 8, zv(w4)))) return st;
-    if ((st = conv_backward(n, 7, zv(w4)))) return st;
-    if ((st = relu_grad(n, V(n->g_a4, w4, 0), none, V(n->a4, w4, 0), w4, H / 8, W / 8, zv(w4)))) return st;
-    if ((st = conv_backward(n, 6, zv(w4)))) return st;
+    if ((st = conv_backward(n, 7, V(n->g_m4, w4, 0), V(n->a4, w4, 0)))) return st;
+    if ((st = conv_backward(n, 6, V(n->g_a4, w4, 0)))) return st;
     // encoder: skip gradient + pooled gradient, through the ReLU
     if ((st = relu_grad(n, V(n->g_cat3, w4 + w3, w4), V(n->g_p3, w3, 0), V(n->cat3, w4 + w3, w4), w3,
                         H / 4, W / 4, zv(w3)))) return st;
-    if ((st = conv_backward(n, 5, zv(w3)))) return st;
-    if ((st = relu_grad(n, V(n->g_a3, w3, 0), none, V(n->a3, w3, 0), w3, H / 4, W / 4, zv(w3)))) return st;
-    if ((st = conv_backward(n, 4, zv(w3)))) return st;
+    if ((st = conv_backward(n, 5, zv(w3), V(n->a3, w3, 0)))) return st;
+    if ((st = conv_backward(n, 4, V(n->g_a3, w3, 0)))) return st;
     if ((st = relu_grad(n, V(n->g_cat2, w3 + w2, w3), V(n->g_p2, w2, 0), V(n->cat2, w3 + w2, w3), w2,
                         H / 2, W / 2, zv(w2)))) return st;
-    if ((st = conv_backward(n, 3, zv(w2)))) return st;
-    if ((st = relu_grad(n, V(n->g_a2, w2, 0), none, V(n->a2, w2, 0), w2, H / 2, W / 2, zv(w2)))) return st;
-    if ((st = conv_backward(n, 2, zv(w2)))) return st;
+    if ((st = conv_backward(n, 3, zv(w2), V(n->a2, w2, 0)))) return st;
+    if ((st = conv_backward(n, 2, V(n->g_a2, w2, 0)))) return st;
     if ((st = relu_grad(n, V(n->g_cat1, w2 + w1, w2), V(n->g_p1, w1, 0), V(n->cat1, w2 + w1, w2), w1, H,
                         W, zv(w1)))) return st;
-    if ((st = conv_backward(n, 1, zv(w1)))) return st;
-    if ((st = relu_grad(n, V(n->g_a1, w1, 0), none, V(n->a1, w1, 0), w1, H, W, zv(w1)))) return st;
-    if ((st = conv_backward(n, 0, zv(w1)))) return st;
+    if ((st = conv_backward(n, 1, zv(w1), V(n->a1, w1, 0)))) return st;
+    if ((st = conv_backward(n, 0, V(n->g_a1, w1, 0)))) return st;
     if (loss) {
         double sum = 0.0;
         CLBM_HIP(hipMemcpyAsync(&sum, n->loss, sizeof(double), hipMemcpyDeviceToHost, n->stream));

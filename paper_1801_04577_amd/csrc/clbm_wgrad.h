@@ -26,6 +26,7 @@ struct WgradArgs {
     int zC;
     const bf16* x;
     int xC, xoff;
+    int zocts, xocts;           // octets of channels that are stored (the others are zero)
     int H, W, P;
     int co_blocks, ci_blocks;   // blocks of 16 NA x 32 channels
     int pixels, splits;         // pixels per split (a multiple of 32) and their number
@@ -90,6 +91,7 @@ __global__ void __launch_bounds__(192) k_wgrad(const WgradArgs a)
     const int oct = tid & 3, px = tid >> 2;   // staged octet and pixel (the first of two)
     const bf16* xb = a.x + a.xoff + cib * 32 + 8 * oct;
     const bf16* zb = a.dz + cob * 16 * NA + 8 * oct;
+    const bool xin = cib * 4 + oct < a.xocts;
     const bf16x8 zero = {};
     if (tid < 4) *reinterpret_cast<bf16x8*>(lds + kZero + 8 * tid) = zero;
     // Ring d holds the input at a distance of (d - 1) rows (WIDE), or the one ring all of it;
@@ -98,7 +100,7 @@ __global__ void __launch_bounds__(192) k_wgrad(const WgradArgs a)
     const int halo = WIDE ? 1 : W + 1;
     auto xload = [&](int d, int q) {
         if (WIDE) q += (d - 1) * W;
-        return q >= 0 && q < a.P ? *reinterpret_cast<const bf16x8*>(xb + (size_t)q * a.xC) : zero;
+        return xin && q >= 0 && q < a.P ? *reinterpret_cast<const bf16x8*>(xb + (size_t)q * a.xC) : zero;
     };
     auto xput = [&](int d, int q, const bf16x8 v) {
         const unsigned slot = (unsigned)q & (RING - 1);
@@ -112,7 +114,7 @@ __global__ void __launch_bounds__(192) k_wgrad(const WgradArgs a)
             const int p = pbeg + st * kWgStep + px + u * kPass;
 #pragma unroll
             for (int k = 0; k < kPlanes; ++k)
-                rz[s][u][k] = p < pend ? *reinterpret_cast<const bf16x8*>(zb + (size_t)p * a.zC + 32 * k) : zero;
+                rz[s][u][k] = p < pend && cob * 2 * NA + 4 * k + oct < a.zocts ? *reinterpret_cast<const bf16x8*>(zb + (size_t)p * a.zC + 32 * k) : zero;
 #pragma unroll
             for (int d = 0; d < kRings; ++d)
                 if (input) rx[s][u][d] = xload(d, p + halo);
