@@ -9,7 +9,7 @@
 //
 // Every output is accumulated in FP32 in one of two orders, which fix its rounding: with
 // the chunk of 32 input channels outermost and the taps inside (k_conv_rows), or with the
-// taps outermost (k_conv_taps).
+// taps outermost (k_conv_tile, k_conv_taps).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,8 +28,8 @@ __device__ __forceinline__ float bf2f(bf16 v) { return (float)v; }
 __device__ __forceinline__ bf16 f2bf(float v) { return (bf16)v; }
 
 // Weights of one direction of a layer as its convolution reads them: per group of 32 output
-// channels, chunk of 32 input channels, tap and row block h one fragment of 1 KB, lane
-// after lane. Row i of block h is channel 8 (i/4) + 4 h + i % 4 of the group.
+// channels, chunk of 32 input channels and tap (in the order they are accumulated) and row
+// block h one fragment of 1 KB, lane after lane. Row i of block h is channel 8 (i/4) + 4 h + i % 4 of the group.
 struct ConvArgs {
     const bf16* x;       // input, NHWC
     int xC, xoff, Cin;   // channel stride and offset; input channels, a multiple of 32
@@ -204,20 +204,130 @@ __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs 
     }
 }
 
-// Tap-outermost order, for images that k_conv_rows does not tile in its own order. A wave
-// owns MP blocks of 16 consecutive pixels (of the whole batch) and NG groups of 32
-// channels, its operands come from memory, and the fragments of the next D steps (a step
-// is one tap of one chunk) are in flight while one is multiplied: with few waves per CU
-// the time is otherwise the latency of every step's loads.
-template <int MP, int NG, int NH>
+// Tap-outermost order on a staged tile. The pixel block of a workgroup (16 columns x R PY rows
+// of one image, with its halo) is staged in LDS with all its input channels, so each tap
+// reads it there at an offset instead of fetching it again; a wave owns 16 columns x R
+// rows and 32 channels. A step is one tap of one chunk; the weights lie in the order of the
+// steps and come from memory 2 U steps ahead, the pixels of the next step are read while
+// one is multiplied. U divides the chunks, so U steps share a tap and everything that depends
+// on the tap is decided between groups of U: with a decision per step its branches and the
+// exposed LDS read took three times the MFMAs' time. 16 images of 24 x 20, 384 -> 128
+// channels: 27 us, 42 with every tap's pixels from memory.
+// LDS: [chunk][pixel][32 channels], octets rotated as in k_conv_rows.
+template <int R, int CW, int PY, int NH, int U>
+__global__ void __launch_bounds__(64 * CW * PY) k_conv_tile(const ConvArgs a)
+{
+    constexpr int NT = 64 * CW * PY, HX = 18, HY = R * PY + 2, NPIX = HX * HY;
+    extern __shared__ __attribute__((aligned(16))) bf16 st[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), cw = wave % CW, wy = wave / CW;
+    const int nbx = (a.W + 15) / 16, nby = (a.H + R * PY - 1) / (R * PY);
+    const int bx = blockIdx.x % nbx, by = (blockIdx.x / nbx) % nby, img = blockIdx.x / (nbx * nby);
+    const int x0 = bx * 16, y0 = by * R * PY;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int nch = a.Cin / kKChunk, steps = 9 * nch;
+    const bf16* wp = a.w + (size_t)(blockIdx.y * CW + cw) * nch * kChunkW + lane * 8;
+    bf16x8 w[2 * U][NH];
+    auto weights = [&](int d, int s) {   // past the last step: the last again
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+            w[d][h] = *reinterpret_cast<const bf16x8*>(wp + (size_t)min(s, steps - 1) * (2 * kFrag) + h * kFrag);
+    };
+#pragma unroll
+    for (int d = 0; d < 2 * U; ++d) weights(d, d);
+    // stage: octets of a pixel are neighbouring threads; whole chunks of a pixel one after the other
+    const bf16* xi = a.x + (size_t)img * a.H * a.W * a.xC + a.xoff;
+    const int octs = a.octs, per = 4 * nch;
+    const bf16x8 zero = {};
+    for (int t = tid; t < NPIX * per; t += NT) {
+        const int px = t / per, o = t - px * per, c = o >> 2, oct = o & 3;
+        const int hy = px / HX, hx = px - hy * HX, sy = y0 + hy - 1, sx = x0 + hx - 1;
+        const bool in = o < octs && sy >= 0 && sy < a.H && sx >= 0 && sx < a.W;
+        *reinterpret_cast<bf16x8*>(&st[(c * NPIX + px) * kKChunk + ((oct ^ ((hx >> 2) & 3)) << 3)]) =
+            in ? *reinterpret_cast<const bf16x8*>(xi + (size_t)(sy * a.W + sx) * a.xC + 8 * o) : zero;
+    }
+    unsigned base[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx) {
+        const int hx = r16 + dx;
+        base[dx] = (unsigned)((wy * R * HX + hx) * kKChunk + ((g ^ ((hx >> 2) & 3)) << 3));
+    }
+    // first pixel of the group that starts with chunk c of tap (dy, dx)
+    int dy = 0, dx = 0, c = 0;
+    auto group = [&]() {
+        return st + (c * NPIX + dy * HX) * kKChunk + (dx == 0 ? base[0] : dx == 1 ? base[1] : base[2]);
+    };
+    auto turn = [&]() {
+        c += U;
+        if (c == nch) {
+            c = 0;
+            if (++dx == 3) {
+                dx = 0;
+                if (++dy == 3) dy = 0;   // past the last step: the first again
+            }
+        }
+    };
+    bf16x8 v[2][R];
+    auto pixels = [&](int d, const bf16* p) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[d][r] = *reinterpret_cast<const bf16x8*>(p + r * HX * kKChunk);
+    };
+    f32x4 acc[R][NH];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int h = 0; h < NH; ++h) acc[r][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int n0 = (blockIdx.y * CW + cw) * 32 + 8 * g;
+    float bias[4 * NH];
+    conv_bias<NH>(a, n0, bias);
+    __syncthreads();
+    const bf16* p = group();
+    pixels(0, p);
+    for (int s = 0; s < steps; s += 2 * U) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (half == 1 && s + U >= steps) break;
+            turn();
+            const bf16* next = group();
+#pragma unroll
+            for (int d = half * U; d < (half + 1) * U; ++d) {
+                const int k = d - half * U + 1;
+                pixels((d + 1) & 1, k < U ? p + k * NPIX * kKChunk : next);
+                __builtin_amdgcn_sched_barrier(0);   // the reads stay ahead of the multiply
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int h = 0; h < NH; ++h)
+                        acc[r][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[d][h], v[d & 1][r], acc[r][h], 0, 0, 0);
+                weights(d, s + d + 2 * U);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            p = next;
+        }
+    }
+    const int xx = x0 + r16;
+    if (xx >= a.W) return;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int yy = y0 + wy * R + r, rem = yy * a.W + xx;
+        if (yy < a.H) conv_store<NH>(a, acc[r], bias, n0, (size_t)img * a.H * a.W + rem, img, rem);
+    }
+}
+
+// Tap-outermost order where there is too little work for tiles, or a tile with all its
+// channels does not fit in LDS. A wave owns MP blocks of 16 consecutive pixels (of the whole
+// batch) and 32 channels, and its operands come from memory, D steps ahead: bound by the
+// latency of those loads (four 32 x 32 images, the six layers at 8 x 8 and 4 x 4: 7 to 21 us
+// each; loaded in the step that multiplies them, 62 us on average).
+template <int MP, int NH>
 __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
 {
-    constexpr int D = 4;
+    constexpr int D = MP == 1 ? 9 : 3;   // divides the number of steps
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int r16 = lane & 15, g = lane >> 4;
     const int HW = a.H * a.W, nch = a.Cin / kKChunk, steps = 9 * nch;
-    const int groups = (a.N + 32 * NG - 1) / (32 * NG);
+    const int groups = (a.N + 31) / 32;
     // waves of a workgroup: neighbouring channel groups first (they share the pixels)
     const int id = blockIdx.x * 4 + wave, ng = id % groups;
     const int p0 = id / groups * 16 * MP;
@@ -233,12 +343,12 @@ __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
         xb[j] = a.x + (size_t)p * a.xC + a.xoff + (g < a.octs ? 8 * g : 0);
     }
     const bf16x8 zero = {};
-    const bf16* wp = a.w + (size_t)ng * NG * nch * kChunkW + lane * 8;
-    bf16x8 va[D][MP], vw[D][NG][NH];
+    const bf16* wp = a.w + (size_t)ng * nch * kChunkW + lane * 8;
+    bf16x8 va[D][MP], vw[D][NH];
     bool in[D][MP];
-    int lt = 0, lc = 0;   // tap and chunk of the next step to load
+    int ls = 0, ly = 0, lx = 0, lc = 0;   // next step to load: its tap (row, column) and chunk
     auto load = [&](int d) {
-        const int dy = lt / 3 - 1, dx = lt % 3 - 1;
+        const int dy = ly - 1, dx = lx - 1;
 #pragma unroll
         for (int j = 0; j < MP; ++j) {
             in[d][j] = g < a.octs && (unsigned)(py[j] + dy) < (unsigned)a.H && (unsigned)(px[j] + dx) < (unsigned)a.W;
@@ -247,43 +357,37 @@ __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
             va[d][j] = *reinterpret_cast<const bf16x8*>(xb[j] + off + lc * kKChunk);
         }
 #pragma unroll
-        for (int n = 0; n < NG; ++n)
-#pragma unroll
-            for (int h = 0; h < NH; ++h)
-                vw[d][n][h] = *reinterpret_cast<const bf16x8*>(wp + (size_t)(n * nch + lc) * kChunkW
-                                                               + (lt * 2 + h) * kFrag);
-        if (++lc == nch) {
-            lc = 0;
-            ++lt;
-        }
+        for (int h = 0; h < NH; ++h)
+            vw[d][h] = *reinterpret_cast<const bf16x8*>(wp + (size_t)min(ls, steps - 1) * (2 * kFrag) + h * kFrag);
+        ++ls;
+        const bool turn = ++lc == nch;   // past the last step the first again
+        lc = turn ? 0 : lc;
+        lx += turn;
+        const bool down = lx == 3;
+        lx = down ? 0 : lx;
+        ly += down;
+        ly = ly == 3 ? 0 : ly;
     };
-    f32x4 acc[MP][NG][NH];
+    f32x4 acc[MP][NH];
 #pragma unroll
     for (int j = 0; j < MP; ++j)
 #pragma unroll
-        for (int n = 0; n < NG; ++n)
+        for (int h = 0; h < NH; ++h) acc[j][h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int h = 0; h < NH; ++h) acc[j][n][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-        if (d < steps) load(d);
-    float bias[NG][4 * NH];
-#pragma unroll
-    for (int n = 0; n < NG; ++n) conv_bias<NH>(a, (ng * NG + n) * 32 + 8 * g, bias[n]);
+    for (int d = 0; d < D; ++d) load(d);
+    float bias[4 * NH];
+    conv_bias<NH>(a, ng * 32 + 8 * g, bias);
     for (int s = 0; s < steps; s += D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            if (s + d >= steps) break;
 #pragma unroll
             for (int j = 0; j < MP; ++j) {
                 const bf16x8 v = in[d][j] ? va[d][j] : zero;
 #pragma unroll
-                for (int n = 0; n < NG; ++n)
-#pragma unroll
-                    for (int h = 0; h < NH; ++h)
-                        acc[j][n][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vw[d][n][h], v, acc[j][n][h], 0, 0, 0);
+                for (int h = 0; h < NH; ++h)
+                    acc[j][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vw[d][h], v, acc[j][h], 0, 0, 0);
             }
-            if (s + d + D < steps) load(d);
+            load(d);
         }
     }
 #pragma unroll
@@ -291,10 +395,7 @@ __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
         const int p = p0 + 16 * j + r16;
         if (p >= a.P) continue;
         const int img = p / HW;
-#pragma unroll
-        for (int n = 0; n < NG; ++n)
-            if ((ng * NG + n) * 32 < a.N)
-                conv_store<NH>(a, acc[j][n], bias[n], (ng * NG + n) * 32 + 8 * g, (size_t)p, img, p - img * HW);
+        conv_store<NH>(a, acc[j], bias, ng * 32 + 8 * g, (size_t)p, img, p - img * HW);
     }
 }
 
@@ -306,6 +407,7 @@ struct PrepLayer {
     size_t woff;
     bf16 *wf, *wb;
     int cin, cout, chunks_f, chunks_b;
+    int taps;     // the tap is the outer index, not the chunk
     int first;    // index of the layer's first lane fragment
     int lanes_f;  // lane fragments of the forward direction
 };
@@ -326,8 +428,8 @@ static __global__ void __launch_bounds__(256) k_weight_prep(const float* __restr
     const bool back = k >= L.lanes_f;
     if (back) k -= L.lanes_f;
     const int lane = k & 63, h = (k >> 6) & 1, rest = k >> 7;
-    const int tap = rest % 9, chunks = back ? L.chunks_b : L.chunks_f;
-    const int c = rest / 9 % chunks, grp = rest / 9 / chunks;
+    const int chunks = back ? L.chunks_b : L.chunks_f, grp = rest / (9 * chunks), step = rest - grp * 9 * chunks;
+    const int tap = L.taps ? step / chunks : step % 9, c = L.taps ? step % chunks : step / 9;
     const int i = lane & 15, n = grp * 32 + 8 * (i >> 2) + 4 * h + (i & 3), k0 = c * kKChunk + 8 * (lane >> 4);
     const float* W = params + L.woff;
     bf16x8 o;

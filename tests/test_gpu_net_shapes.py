@@ -18,6 +18,7 @@ CASES = [  # batch, height, width, cin, cout, widths
     (8, 16, 256, 3, 5, (64, 32, 96, 64)),
     (32, 32, 16, 32, 16, (96, 64, 32, 160)),
     (4, 32, 128, 9, 4, (64, 128, 64, 128)),
+    (128, 40, 24, 8, 3, (96, 32, 128, 160)),
 ]
 
 
