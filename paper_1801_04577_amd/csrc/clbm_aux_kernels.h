@@ -156,22 +156,20 @@ __global__ void __launch_bounds__(kDiagBlock) k_diag(const S* __restrict__ src, 
     }
 }
 
+// One workgroup per sum; latency bound. The 19 sums one after the other in one workgroup, each
+// with a barrier per level of its tree, took 20 us.
 static __global__ void __launch_bounds__(256) k_diag_final(const double* __restrict__ partial, int nparts,
-                                                    double* __restrict__ out)
+                                                           double* __restrict__ out)
 {
     __shared__ double lds[256];
-    for (int k = 0; k < kDiagSums; ++k) {
-        double v = 0.0;
-        for (int p = threadIdx.x; p < nparts; p += blockDim.x) v += partial[(size_t)p * kDiagSums + k];
-        lds[threadIdx.x] = v;
-        __syncthreads();
-        for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) lds[threadIdx.x] += lds[threadIdx.x + s];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out[k] = lds[0];
-        __syncthreads();
-    }
+    const int k = blockIdx.x, t = threadIdx.x;
+    double v = 0.0;
+    for (int p = t; p < nparts; p += 256) v += partial[(size_t)p * kDiagSums + k];
+    lds[t] = v;
+    __syncthreads();
+    if (t >= 64) return;
+    v = wave_sum((lds[t] + lds[t + 128]) + (lds[t + 64] + lds[t + 192]));
+    if (t == 0) out[k] = v;
 }
 
 }  // namespace clbm

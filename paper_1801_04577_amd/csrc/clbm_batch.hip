@@ -906,7 +906,7 @@ clbm_status clbm_batch_diagnostics(clbm_batch* b, int i, clbm_diag* out)
                            (const float*)(uintptr_t)I.buf[b->parity], I.c, (float*)(uintptr_t)I.snap, 0,
                            b->d_dpart);
     CLBM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, b->stream, b->d_dpart, blocks, b->d_dres);
+    hipLaunchKernelGGL(k_diag_final, dim3(kDiagSums), dim3(256), 0, b->stream, b->d_dpart, blocks, b->d_dres);
     CLBM_HIP(hipGetLastError());
     double r[kDiagSums];
     CLBM_HIP(hipMemcpyAsync(r, b->d_dres, sizeof r, hipMemcpyDeviceToHost, b->stream));

@@ -742,7 +742,7 @@ clbm_status diagnostics_into(clbm_handle* h, double* partial, double* result, cl
         hipLaunchKernelGGL(k_diag<float>, dim3(blocks), dim3(kDiagBlock), 0, h->stream,
                            (const float*)h->buf[h->cur], h->c, h->snap, have, partial);
     CLBM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(256), 0, h->stream, partial, blocks, result);
+    hipLaunchKernelGGL(k_diag_final, dim3(kDiagSums), dim3(256), 0, h->stream, partial, blocks, result);
     CLBM_HIP(hipGetLastError());
     double r[kDiagSums];
     CLBM_HIP(hipMemcpyAsync(r, result, sizeof r, hipMemcpyDeviceToHost, h->stream));
