@@ -683,6 +683,15 @@ clbm_status wgrad_ring(clbm_net* n, const WgradArgs& g)
     return CLBM_OK;
 }
 
+template <int NA>
+clbm_status wgrad_octets(clbm_net* n, const WgradArgs& g)
+{
+    const dim3 grid((g.splits + 7) / 8 * 8 * g.co_blocks * g.ci_blocks), block(384);
+    hipLaunchKernelGGL((k_wgrad_octets<NA>), grid, block, OctetGeom<NA>::lds(g.W), n->stream, g);
+    CLBM_HIP(hipGetLastError());
+    return CLBM_OK;
+}
+
 // Weight and bias gradients of a layer.
 template <int NA>
 clbm_status wgrad_launch(clbm_net* n, const Layer& l, TView dz)
@@ -706,9 +715,12 @@ clbm_status wgrad_launch(clbm_net* n, const Layer& l, TView dz)
     g.bpart = n->bpart;
     // the ring holds two rows and two steps: rows of up to 159 pixels in 512
     const int need = 2 * l.W + 2 + 2 * kWgStep;
-    const clbm_status st = need <= 256   ? wgrad_ring<NA, 256, false>(n, g)
-                           : need <= 512 ? wgrad_ring<NA, 512, false>(n, g)
-                                         : wgrad_ring<NA, 256, true>(n, g);
+    // one workgroup per CU at most: the latency of each counts, not the chip's LDS traffic
+    const bool few = g.splits * g.co_blocks * g.ci_blocks <= 256;
+    const clbm_status st = few && l.W % 8 == 0 && OctetGeom<NA>::lds(l.W) <= 160 * 1024 ? wgrad_octets<NA>(n, g)
+                           : need <= 256                                            ? wgrad_ring<NA, 256, false>(n, g)
+                           : need <= 512                                            ? wgrad_ring<NA, 512, false>(n, g)
+                                                                                    : wgrad_ring<NA, 256, true>(n, g);
     if (st != CLBM_OK) return st;
     const size_t weights = (size_t)l.cout_kpad * 9 * l.cin_pad;
     hipLaunchKernelGGL(k_wgrad_reduce<NA>, dim3((unsigned)(weights / 64 + (l.cout_kpad + 63) / 64)), dim3(64), 0,

@@ -6,6 +6,8 @@
 // lanes), so a tap is a constant LDS offset and nothing is staged more than once.
 #pragma once
 
+#include <type_traits>
+
 #include "clbm_conv.h"
 
 namespace clbm {
@@ -53,9 +55,10 @@ constexpr int kWgStep = 96;   // pixels staged per step: three chunks of K = 32
 
 // A workgroup owns 16 NA x 32 channels and the consecutive pixels of one split. Wave dy
 // takes the three taps of kernel row dy, so a chunk costs it NA + 6 fragment reads for 6 NA
-// MFMAs. The reads bound it: a transpose read of 512 bytes holds the LDS for 16 cycles (the
-// LDS instructions of the 32 -> 32 layer at 16 cycles each are its whole time), so waves of
-// 16 input channels, which read more per MFMA, were slower although twice as many. The input lies in LDS as a ring over consecutive pixels of
+// MFMAs. A wave's chain of reads and multiplies bounds it, covered by the other workgroup of
+// the CU: reading a chunk ahead takes the registers of that one (64 -> 64 at 64^2: 34 us
+// against 21), and waves of 16 input channels, which read more per MFMA, were slower although
+// twice as many. The input lies in LDS as a ring over consecutive pixels of
 // the batch that spans the rows above and below the current pixels: a pixel is staged once
 // and a tap is a constant distance in the ring (rows too long for that have a ring per
 // kernel row, and are staged three times). A lane whose pixel has no such neighbour reads
@@ -263,6 +266,220 @@ __global__ void __launch_bounds__(192) k_wgrad(const WgradArgs a)
 #pragma unroll
         for (int i = 0; i < NA; ++i)
             reinterpret_cast<f32x4*>(a.bpart)[((size_t)split * a.co_blocks + cob) * (4 * NA) + 4 * i + (lane >> 4)] = bacc[i];
+}
+
+// Geometry of k_wgrad_octets: pixels staged per step, and LDS bytes of one channel's pixels,
+// the last 16 of them zeros. Channels start a multiple of 128 bytes and 16 apart, octets
+// of channels 32 more: the eight channels that a group of lanes reads cover all banks, and so do the
+// four octets x two pixel groups that it writes.
+template <int NA>
+struct OctetGeom {
+    static constexpr int S = NA == 4 ? 128 : 192;   // (NA/2 + 1 planes) x S/8 x 4 octets: 192 items
+    static constexpr int HALO = 8;   // pixels kept on either side
+    static constexpr int ZS = 2 * S + 16;
+    static constexpr int Z = 16 * NA * ZS + 64 * NA;
+    __host__ __device__ static int ring(int W) { return 2 * W + 2 * HALO + 2 * S; }
+    __host__ __device__ static int xs(int W) { return (2 * ring(W) + 127) / 128 * 128 + 16; }
+    __host__ __device__ static int x_bytes(int W) { return 32 * xs(W) + 128; }
+    static size_t lds(int W) { return (size_t)x_bytes(W) + 2 * Z; }
+};
+
+// Rows of whole octets of pixels. A workgroup owns 16 NA x 32 channels and the consecutive pixels
+// of one split; wave (dy, j) takes the three taps of kernel row dy and half j of the input
+// channels. Operands are transposed on their way to LDS: an item is eight pixels x
+// eight channels, 16-byte loads of a pixel's channels and 16-byte stores of a channel's
+// pixels, so a fragment (one channel, eight consecutive pixels per lane) is one plain 16-byte
+// read. The taps to the left and right are the same fragment shifted by one pixel with
+// the neighbouring pair from LDS. The input is a ring over consecutive pixels of the batch that
+// holds the rows above and below, staged once; an octet lies in one row, so a pixel outside
+// the image is a whole fragment or a neighbouring pair, read from the zeros behind the lane's
+// channel instead. Two steps are in registers or on their way (the halves of the
+// workgroup stage alternate ones), one barrier per step; the fragments of the next chunk are
+// read while one is multiplied. It reads more of LDS per MFMA than k_wgrad and is the faster one
+// where a CU has a single workgroup: 32 -> 32 channels at batch 32 on 128^2, 256 workgroups:
+// 25 against 33 us; with 512 of 64 x 32 channels 26 against 21 us.
+template <int NA>
+__global__ void __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(2))) k_wgrad_octets(const WgradArgs a)
+{
+    using G = OctetGeom<NA>;
+    constexpr int S = G::S, ZS = G::ZS, HALO = G::HALO, kZPlanes = NA / 2;
+    extern __shared__ __attribute__((aligned(128))) char oct_lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), dy = wave % 3, jb = wave / 3;
+    const int blocks = a.co_blocks * a.ci_blocks;
+    const int local = blockIdx.x >> 3, split = (blockIdx.x & 7) + 8 * (local / blocks), blk = local % blocks;
+    if (split >= a.splits) return;
+    const int cob = blk % a.co_blocks, cib = blk / a.co_blocks;
+    const int pbeg = split * a.pixels, pend = min(a.P, pbeg + a.pixels), chunks = (pend - pbeg) / 32;
+    const int W = a.W, H = a.H, ring = G::ring(W), XS = G::xs(W), last = a.P - 8;
+    char* const zlds = oct_lds + G::x_bytes(W);
+    const bf16x8 zero = {};
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    // eight pixels x eight channels in, a channel's eight pixels out
+    auto store = [](char* to, int stride, const bf16x8 (&v)[8]) {
+        u32x4 in[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) in[j] = __builtin_bit_cast(u32x4, v[j]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            u32x4 out;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                out[i] = __builtin_amdgcn_perm(in[2 * i + 1][k / 2], in[2 * i][k / 2], k % 2 ? 0x07060302u : 0x05040100u);
+            *reinterpret_cast<u32x4*>(to + k * stride) = out;
+        }
+    };
+    // this thread's item of a step: octet o of the channels of a plane, pixel group
+    const int item = tid - 192 * jb, o = item & 3, pg = (item >> 2) % (S / 8), plane = item / (S / 2);
+    const bool isx = plane == kZPlanes;
+    const bool have = isx ? cib * 4 + o < a.xocts : cob * 2 * NA + 4 * plane + o < a.zocts;
+    const int istride = isx ? a.xC : a.zC;
+    const bf16* const isrc = isx ? a.x + a.xoff + cib * 32 + 8 * o : a.dz + cob * 16 * NA + plane * 32 + 8 * o;
+    const int ipix = pbeg + 8 * pg + (isx ? W + HALO : 0);   // its first pixel in step 0
+    // Pixels after the split's (gradient) or the batch's last (input) are multiplied by no lane:
+    // any pixel's channels do.
+    bf16x8 v[8];
+    auto load = [&](const bf16* src, int p, int stride) {
+        src += (size_t)max(0, min(p, last)) * stride;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const bf16x8*>(src + (size_t)j * stride);
+    };
+    auto fetch = [&](int st) {
+        if (have) load(isrc, ipix + st * S, istride);
+    };
+    char* const zrow = zlds + (plane * 4 + o) * (8 * ZS + 32) + 16 * pg;
+    char* const xrow = oct_lds + o * (8 * XS + 32);
+    int slot = 2 * W + 2 * HALO + 8 * pg + (jb == 0 ? 2 * S : S);   // ring place of its next put
+    slot = slot >= ring ? slot - ring : slot;
+    auto put = [&](int st) {
+        if (have) {
+            if (isx) store(xrow + 2 * slot, XS, v);
+            else store(zrow + (st & 1) * G::Z, ZS, v);
+        }
+        slot += 2 * S;
+        slot = slot >= ring ? slot - ring : slot;
+    };
+    const int steps = (chunks * 32 + S - 1) / S;
+    // channels that are not stored, and the pixels outside the image, read as zeros
+    if (cib * 4 + 4 > a.xocts || cob * 2 * NA + 2 * NA > a.zocts) {
+        for (int t = tid; t < (G::x_bytes(W) + 2 * G::Z) / 16; t += 384) reinterpret_cast<bf16x8*>(oct_lds)[t] = zero;
+        __syncthreads();
+    }
+    if (tid < 32) *reinterpret_cast<bf16x8*>(oct_lds + tid * XS + (tid >> 3) * 32 + XS - 16) = zero;
+    // input of the first step with the rows around it: ring places 0 .. 2 W + 2 HALO + S
+    for (int t = tid; t < (2 * W + 2 * HALO + S) / 2; t += 384) {
+        const int oc = t & 3;
+        if (cib * 4 + oc < a.xocts) {
+            load(a.x + a.xoff + cib * 32 + 8 * oc, pbeg - W - HALO + 2 * (t & ~3), a.xC);
+            store(oct_lds + oc * (8 * XS + 32) + 4 * (t & ~3), XS, v);
+        }
+    }
+    if (jb == 0 && !isx && have) {
+        fetch(0);
+        store(zrow, ZS, v);
+    }
+    if (2 - jb < steps) fetch(2 - jb);
+    f32x4 acc[3][NA], bacc[NA];
+    const f32x4 fz = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NA; ++i) acc[0][i] = acc[1][i] = acc[2][i] = bacc[i] = fz;
+    bf16x8 ones;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ones[i] = (bf16)1.f;
+    const bool bias = cib == 0 && dy == 1 && jb == 0;
+    // the next chunk's octet of pixels of this lane: row and column of the image and byte in a
+    // channel's ring
+    const int r16 = lane & 15, g = lane >> 4;
+    const int rem = (pbeg + 8 * g) % (H * W);
+    int y = rem / W, x = rem - y * W;
+    unsigned at = 2 * (dy * W + HALO + 8 * g);
+    const unsigned end = 2 * ring, none = XS - 16;
+    const int down = 32 / W % H, right = 32 % W;
+    const char* const xl = oct_lds + (16 * jb + r16) * XS + (2 * jb + (r16 >> 3)) * 32;
+    const unsigned zl = r16 * ZS + (r16 >> 3) * 32 + 16 * g;
+    struct Frags {
+        bf16x8 z[NA];
+        u32x4 x;
+        unsigned left, right;
+    } f[2];
+    auto read = [&](Frags& f, const char* z, int k) {
+        const bool vy = (unsigned)(y + dy - 1) < (unsigned)H;
+        const unsigned mid = vy ? at : none;
+        const unsigned lef = vy && x > 0 ? (at ? at : end) - 4 : none;
+        const unsigned rig = vy && x + 8 < W ? (at + 16 == end ? 0 : at + 16) : none;
+        x += right;
+        const bool next = x >= W;
+        x = next ? x - W : x;
+        y += down + next;
+        y = y >= H ? y - H : y;
+        at += 64;
+        at = at >= end ? at - end : at;
+        f.x = *reinterpret_cast<const u32x4*>(xl + mid);
+        f.left = *reinterpret_cast<const unsigned*>(xl + lef);
+        f.right = *reinterpret_cast<const unsigned*>(xl + rig);
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+            f.z[i] = *reinterpret_cast<const bf16x8*>(z + zl + k * 64 + i * (16 * ZS + 64));
+    };
+    auto multiply = [&](const Frags& f, auto with_bias) {
+        const u32x4 c = f.x;
+        const unsigned m1 = __builtin_amdgcn_alignbit(c[1], c[0], 16), m2 = __builtin_amdgcn_alignbit(c[2], c[1], 16);
+        const unsigned m3 = __builtin_amdgcn_alignbit(c[3], c[2], 16);
+        const bf16x8 bx[3] = {
+            __builtin_bit_cast(bf16x8, u32x4{__builtin_amdgcn_alignbit(c[0], f.left, 16), m1, m2, m3}),
+            __builtin_bit_cast(bf16x8, c),
+            __builtin_bit_cast(bf16x8, u32x4{m1, m2, m3, __builtin_amdgcn_alignbit(f.right, c[3], 16)})};
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                acc[dx][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.z[i], bx[dx], acc[dx][i], 0, 0, 0);
+        if constexpr (with_bias.value)
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                bacc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.z[i], ones, bacc[i], 0, 0, 0);
+    };
+    // the chunks of a step: fragments of the next are read while one is multiplied (left to
+    // the compiler, each chunk waited for its own)
+    auto step = [&](const char* z, int n, auto with_bias) {
+        read(f[0], z, 0);
+        if (n == S / 32) {
+#pragma unroll
+            for (int k = 0; k < S / 32; ++k) {
+                if (k + 1 < S / 32) read(f[(k + 1) & 1], z, k + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(f[k & 1], with_bias);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            for (int k = 0; k < n; ++k) {
+                multiply(f[0], with_bias);
+                if (k + 1 < n) read(f[0], z, k + 1);
+            }
+        }
+    };
+    __syncthreads();
+    for (int st = 0; st < steps; ++st) {
+        const int n = min(S / 32, chunks - st * (S / 32));
+        const char* z = zlds + (st & 1) * G::Z;
+        if (bias) step(z, n, std::true_type{});
+        else step(z, n, std::false_type{});
+        if (jb != (st & 1)) {
+            if (st + 1 < steps) put(st + 1);
+            if (st + 3 < steps) fetch(st + 3);
+        }
+        __syncthreads();
+    }
+    f32x4* out = reinterpret_cast<f32x4*>(a.part) + ((size_t)split * blocks + blk) * (9 * NA * 2 * 64) + lane;
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+        for (int i = 0; i < NA; ++i) out[(((dy * 3 + dx) * NA + i) * 2 + jb) * 64] = acc[dx][i];
+    // every column of the product with ones holds the sum; rows 4 (lane / 16) .. + 3
+    if (bias && r16 == 0)
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+            reinterpret_cast<f32x4*>(a.bpart)[((size_t)split * a.co_blocks + cob) * (4 * NA) + 4 * i + g] = bacc[i];
 }
 
 // Sums of the split partials in split order, written to the canonical gradient
