@@ -30,6 +30,20 @@ __device__ __forceinline__ bf16 f2bf(float v) { return (bf16)v; }
 // Weights of one direction of a layer as its convolution reads them: per group of 32 output
 // channels, chunk of 32 input channels and tap (in the order they are accumulated) and row
 // block h one fragment of 1 KB, lane after lane. Row i of block h is channel 8 (i/4) + 4 h + i % 4 of the group.
+// What an epilogue does besides (kPostPool) or instead of writing its output: everything that the
+// network does between two convolutions, on values still in registers and rounded to bf16
+// as they would have been stored. Pool and Sum need 2 x 2 pixels in one wave: rows are in its
+// registers, columns in neighbouring lanes. As kernels of their own these passes took 150 us of
+// a training step at batch 32 on 128^2; in the epilogues they add about 65.
+enum ConvPost : int {
+    kPostNone,
+    kPostPool,     // also the 2 x 2 average, to e (half resolution)
+    kPostUp,       // four copies, to e (double resolution)
+    kPostSum,      // channels below eN: 2 x 2 sums to e (half resolution), zero where mask is not positive at
+                   // the first pixel of the four (the upsampled activations); the others as they are
+    kPostUnpool    // four times a quarter plus e2, zero where mask is not positive, to e (all double resolution)
+};
+
 struct ConvArgs {
     const bf16* x;       // input, NHWC
     int xC, xoff, Cin;   // channel stride and offset; input channels, a multiple of 32
@@ -42,7 +56,12 @@ struct ConvArgs {
     int maskC;
     bf16* y;
     int yC, yoff;
-    float* yf;
+    float *yf, *yf2;     // mode 2: the output, and a second place for it or nullptr
+    int post;            // ConvPost; its views of the operands' channels
+    bf16* e;
+    int eC, eN;
+    const bf16* e2;
+    int e2C;
 };
 
 // Epilogue of one pixel: lane group g = lane / 16 holds channels n0 + 8 g .. + 7.
@@ -53,37 +72,159 @@ __device__ __forceinline__ void conv_bias(const ConvArgs& a, int n, float (&bias
     for (int k = 0; k < 4 * NH; ++k) bias[k] = a.mode != 1 && n + k < a.N ? a.bias[n + k] : 0.f;
 }
 
-template <int NH>
-__device__ __forceinline__ void conv_store(const ConvArgs& a, const f32x4 (&acc)[NH], const float (&bias)[4 * NH],
-                                           int n, size_t p, int img, int rem)
+// The pixel's eight channels as they are stored.
+__device__ __forceinline__ bf16x8 conv_value(const ConvArgs& a, const f32x4 (&acc)[2], const float (&bias)[8])
 {
+    bf16x8 o;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float r = acc[h][v];
+            if (a.mode == 0) r = fmaxf(r + bias[4 * h + v], 0.f);
+            o[4 * h + v] = f2bf(r);
+        }
+    return o;
+}
+
+// Where the pixel (x, y) of image img and the rows below it go and find their masks, as pointers and
+// their steps per row: one 64-bit product each instead of one per pixel and operand.
+template <bool POST>
+struct ConvPlace {
+    bf16 *y, *e;
+    const bf16 *mask, *e2;
+    size_t yS, eS, maskS, e2S;
+    __device__ __forceinline__ ConvPlace(const ConvArgs& a, int n, int img, int py, int px)
+    {
+        const size_t HW = (size_t)a.H * a.W, p = img * HW + (unsigned)(py * a.W + px);
+        const bool twice = POST && (a.post == kPostUp || a.post == kPostUnpool);
+        // double resolution: two rows per row; half: a row per two (eS is per pair)
+        const size_t q = twice ? 4 * img * HW + (size_t)(4 * py) * a.W + 2 * px : p;
+        y = a.y + p * a.yC + a.yoff + n;
+        yS = (size_t)a.W * a.yC;
+        mask = a.mask + q * a.maskC + n;
+        maskS = (size_t)(twice ? 4 * a.W : a.W) * a.maskC;
+        if constexpr (POST) {
+            e = a.e + (twice ? q : img * (HW / 4) + (unsigned)((py / 2) * (a.W / 2) + px / 2)) * a.eC + n;
+            eS = (size_t)(twice ? 4 * a.W : a.W / 2) * a.eC;
+            e2 = a.e2 + q * a.e2C + n;
+            e2S = (size_t)(4 * a.W) * a.e2C;
+        }
+    }
+};
+
+// Row r of a place (its channels n .. n + 7): output and what follows it pixel by pixel.
+template <bool POST>
+__device__ __forceinline__ void conv_pixel(const ConvArgs& a, const ConvPlace<POST>& t, int r, int n, bf16x8 o)
+{
+    if (POST && a.post == kPostSum && n < a.eN) return;
+    if (POST && (a.post == kPostUp || a.post == kPostUnpool)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const size_t at = (size_t)((k >> 1) * 2 * a.W + (k & 1));
+            bf16x8 v = o;
+            if (a.post == kPostUnpool) {
+                const bf16x8 skip = *reinterpret_cast<const bf16x8*>(t.e2 + r * t.e2S + at * a.e2C);
+                const bf16x8 m = *reinterpret_cast<const bf16x8*>(t.mask + r * t.maskS + at * a.maskC);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    v[i] = bf2f(m[i]) > 0.f ? f2bf(bf2f(skip[i]) + 0.25f * bf2f(o[i])) : (bf16)0.f;
+            }
+            *reinterpret_cast<bf16x8*>(t.e + r * t.eS + at * a.eC) = v;
+        }
+        return;
+    }
+    if (a.mask && !(POST && a.post == kPostSum)) {
+        const bf16x8 m = *reinterpret_cast<const bf16x8*>(t.mask + r * t.maskS);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (!(bf2f(m[k]) > 0.f)) o[k] = (bf16)0.f;
+    }
+    *reinterpret_cast<bf16x8*>(t.y + r * t.yS) = o;
+}
+
+// The output layer: pixel (x, y) of image img.
+template <int NH>
+__device__ __forceinline__ void conv_planes(const ConvArgs& a, const f32x4 (&acc)[NH], const float (&bias)[4 * NH],
+                                            int n, int img, int y, int x)
+{
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = n + 4 * h + v;
+            if (c >= a.N) continue;
+            const float r = acc[h][v] + bias[4 * h + v];
+            const size_t at = ((size_t)img * a.N + c) * ((size_t)a.H * a.W) + y * a.W + x;
+            a.yf[at] = r;
+            if (a.yf2) a.yf2[at] = r;
+        }
+}
+
+// 2 x 2 pixels: this lane's column (odd or even) of rows r (r0) and r + 1 (r1), r even, and the
+// neighbouring lane's. The lane of the even column finishes the first four channels, the other the
+// last four.
+__device__ __forceinline__ void conv_pair(const ConvArgs& a, const ConvPlace<true>& t, int r, bool odd, bf16x8 r0,
+                                          bf16x8 r1)
+{
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    const int half = 4 * odd;
+    float sum[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const u32x4 w = __builtin_bit_cast(u32x4, i ? r1 : r0);
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            const unsigned own = odd ? w[2 + d] : w[d], give = odd ? w[d] : w[2 + d];
+            const unsigned got = __builtin_amdgcn_update_dpp(0u, give, 0xB1, 0xF, 0xF, true);   // lanes 1 0 3 2
+            const unsigned left = odd ? got : own, right = odd ? own : got;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const float l = __builtin_bit_cast(float, k ? left & 0xffff0000u : left << 16);
+                const float m = __builtin_bit_cast(float, k ? right & 0xffff0000u : right << 16);
+                float& s = sum[2 * d + k];
+                s = i ? s + l + m : l + m;
+            }
+        }
+    }
+    bf16x4 o;
+    if (a.post == kPostPool) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = f2bf(0.25f * sum[k]);
+    } else {
+        const bf16x4 m = *reinterpret_cast<const bf16x4*>(t.mask + r * t.maskS - (odd ? a.maskC : 0) + half);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = bf2f(m[k]) > 0.f ? f2bf(sum[k]) : (bf16)0.f;
+    }
+    *reinterpret_cast<bf16x4*>(t.e + (r / 2) * t.eS + half) = o;
+}
+
+// R rows of a wave's column x from row y, an even one where 2 x 2 pixels are asked for. POST:
+// a.post is set.
+template <int R, int NH, bool POST>
+__device__ __forceinline__ void conv_rows_store(const ConvArgs& a, const f32x4 (&acc)[R][NH],
+                                                const float (&bias)[4 * NH], int n, int img, int y, int x)
+{
+    if (x >= a.W) return;
     if (a.mode == 2) {
 #pragma unroll
-        for (int h = 0; h < NH; ++h)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int c = n + 4 * h + v;
-                if (c < a.N) a.yf[((size_t)img * a.N + c) * ((size_t)a.H * a.W) + rem] = acc[h][v] + bias[4 * h + v];
-            }
+        for (int r = 0; r < R; ++r)
+            if (y + r < a.H) conv_planes<NH>(a, acc[r], bias, n, img, y + r, x);
         return;
     }
     if constexpr (NH == 2) {
-        bf16x8 o;
+        const ConvPlace<POST> t(a, n, img, y, x);
+        const bool pairs = POST && (a.post == kPostPool || (a.post == kPostSum && n < a.eN));
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float r = acc[h][v];
-                if (a.mode == 0) r = fmaxf(r + bias[4 * h + v], 0.f);
-                o[4 * h + v] = f2bf(r);
-            }
-        if (a.mask) {
-            const bf16x8 m = *reinterpret_cast<const bf16x8*>(a.mask + p * a.maskC + n);
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (!(bf2f(m[k]) > 0.f)) o[k] = (bf16)0.f;
+        for (int r = 0; r < R; r += 2) {
+            if (y + r >= a.H) break;
+            const bf16x8 v0 = conv_value(a, acc[r], bias), v1 = conv_value(a, acc[r + 1], bias);
+            conv_pixel<POST>(a, t, r, n, v0);
+            if (y + r + 1 < a.H) conv_pixel<POST>(a, t, r + 1, n, v1);
+            if constexpr (POST)
+                if (pairs) conv_pair(a, t, r, x & 1, v0, v1);
         }
-        *reinterpret_cast<bf16x8*>(a.y + p * a.yC + a.yoff + n) = o;
     }
 }
 
@@ -99,7 +240,7 @@ __device__ __forceinline__ void conv_store(const ConvArgs& a, const f32x4 (&acc)
 // its weights replaced tap row by tap row while the current chunk is multiplied.
 // LDS: [pixel][32 channels], the four 16-byte octets of a pixel rotated by its column so
 // that 16 neighbouring pixels cover all banks.
-template <int R, int CW, int PX, int PY, int NH, bool ONE>
+template <int R, int CW, int PX, int PY, int NH, bool ONE, bool POST>
 __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs a)
 {
     constexpr int NT = 64 * CW * PX * PY, HX = 16 * PX + 2, HY = R * PY + 2, NPIX = HX * HY;
@@ -194,14 +335,8 @@ __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs 
         }
     }
     const int xx = x0 + wx * 16 + r16;
-    if (xx >= a.W) return;
     if (!ONE) conv_bias<NH>(a, n0, bias);
-#pragma unroll
-    for (int o = 0; o < R; ++o) {
-        const int yy = y0 + wy * R + o, rem = yy * a.W + xx;
-        if (yy < a.H)
-            conv_store<NH>(a, acc[o], bias, n0, (size_t)img * a.H * a.W + rem, img, rem);
-    }
+    conv_rows_store<R, NH, POST>(a, acc, bias, n0, img, y0 + wy * R, xx);
 }
 
 // Tap-outermost order on a staged tile. The pixel block of a workgroup (16 columns x R PY rows
@@ -214,7 +349,7 @@ __global__ void __launch_bounds__(64 * CW * PX * PY) k_conv_rows(const ConvArgs 
 // exposed LDS read took three times the MFMAs' time. 16 images of 24 x 20, 384 -> 128
 // channels: 27 us, 42 with every tap's pixels from memory.
 // LDS: [chunk][pixel][32 channels], octets rotated as in k_conv_rows.
-template <int R, int CW, int PY, int NH, int U>
+template <int R, int CW, int PY, int NH, int U, bool POST>
 __global__ void __launch_bounds__(64 * CW * PY) k_conv_tile(const ConvArgs a)
 {
     constexpr int NT = 64 * CW * PY, HX = 18, HY = R * PY + 2, NPIX = HX * HY;
@@ -306,12 +441,7 @@ __global__ void __launch_bounds__(64 * CW * PY) k_conv_tile(const ConvArgs a)
         }
     }
     const int xx = x0 + r16;
-    if (xx >= a.W) return;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int yy = y0 + wy * R + r, rem = yy * a.W + xx;
-        if (yy < a.H) conv_store<NH>(a, acc[r], bias, n0, (size_t)img * a.H * a.W + rem, img, rem);
-    }
+    conv_rows_store<R, NH, POST>(a, acc, bias, n0, img, y0 + wy * R, xx);
 }
 
 // Tap-outermost order where there is too little work for tiles, or a tile with all its
@@ -394,8 +524,14 @@ __global__ void __launch_bounds__(256) k_conv_taps(const ConvArgs a)
     for (int j = 0; j < MP; ++j) {
         const int p = p0 + 16 * j + r16;
         if (p >= a.P) continue;
-        const int img = p / HW;
-        conv_store<NH>(a, acc[j], bias, ng * 32 + 8 * g, (size_t)p, img, p - img * HW);
+        const int img = p / HW, rem = p - img * HW, y = rem / a.W;
+        const int n = ng * 32 + 8 * g, x = rem - y * a.W;
+        if (a.mode == 2) {
+            conv_planes<NH>(a, acc[j], bias, n, img, y, x);
+        } else if constexpr (NH == 2) {
+            const ConvPlace<MP == 1> t(a, n, img, y, x);
+            conv_pixel<MP == 1>(a, t, 0, n, conv_value(a, acc[j], bias));
+        }
     }
 }
 

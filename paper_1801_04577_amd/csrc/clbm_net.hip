@@ -49,116 +49,44 @@ __global__ void __launch_bounds__(256) k_pack_input(const float* __restrict__ xi
     *reinterpret_cast<bf16x8*>(x + (size_t)p * xC + c0) = o;
 }
 
-// Elementwise kernels over NHWC channel views. Each thread handles V consecutive
-// channels of one pixel: V = 8 (one 16-byte access) where the channel counts, strides
-// and offsets are multiples of 8, else V = 1. The arithmetic per channel is the same.
-template <int V>
-__device__ __forceinline__ void load_v(const bf16* p, float (&out)[V])
+// 2x2 average pooling of a channel view, for the layers whose epilogue cannot (ConvPost).
+// A thread handles eight channels of one pixel.
+__global__ void __launch_bounds__(256) k_avgpool(const bf16* __restrict__ x, int xC, int C, int H, int W, int B,
+                                                 bf16* __restrict__ y, int yC)
 {
-    if constexpr (V == 8) {
-        const bf16x8 t = *reinterpret_cast<const bf16x8*>(p);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) out[i] = bf2f(t[i]);
-    } else {
-        out[0] = bf2f(p[0]);
-    }
-}
-
-template <int V>
-__device__ __forceinline__ void store_v(bf16* p, const float (&in)[V])
-{
-    if constexpr (V == 8) {
-        bf16x8 t;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t[i] = f2bf(in[i]);
-        *reinterpret_cast<bf16x8*>(p) = t;
-    } else {
-        p[0] = f2bf(in[0]);
-    }
-}
-
-// 2x2 average pooling and nearest 2x upsampling on channel views.
-template <int V>
-__global__ void k_avgpool(const bf16* __restrict__ x, int xC, int xoff, int C, int H, int W,
-                          int B, bf16* __restrict__ y, int yC, int yoff)
-{
-    const int Ho = H / 2, Wo = W / 2, CV = C / V;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    const int Ho = H / 2, Wo = W / 2, CV = C / 8;
+    const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= B * Ho * Wo * CV) return;
-    const int c = (k % CV) * V, p = k / CV;
+    const int c = (k % CV) * 8, p = k / CV;
     const int b = p / (Ho * Wo), r = p - b * Ho * Wo, oy = r / Wo, ox = r - oy * Wo;
-    const size_t base = (size_t)b * H * W;
-    float v00[V], v01[V], v10[V], v11[V], out[V];
-    load_v<V>(x + (base + (2 * oy) * W + 2 * ox) * xC + xoff + c, v00);
-    load_v<V>(x + (base + (2 * oy) * W + 2 * ox + 1) * xC + xoff + c, v01);
-    load_v<V>(x + (base + (2 * oy + 1) * W + 2 * ox) * xC + xoff + c, v10);
-    load_v<V>(x + (base + (2 * oy + 1) * W + 2 * ox + 1) * xC + xoff + c, v11);
+    const bf16* src = x + ((size_t)b * H * W + (2 * oy) * W + 2 * ox) * xC + c;
+    bf16x8 v[4], o;
 #pragma unroll
-    for (int i = 0; i < V; ++i) out[i] = 0.25f * (v00[i] + v01[i] + v10[i] + v11[i]);
-    store_v<V>(y + (size_t)p * yC + yoff + c, out);
+    for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const bf16x8*>(src + (size_t)((i >> 1) * W + (i & 1)) * xC);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = f2bf(0.25f * (bf2f(v[0][i]) + bf2f(v[1][i]) + bf2f(v[2][i]) + bf2f(v[3][i])));
+    *reinterpret_cast<bf16x8*>(y + (size_t)p * yC + c) = o;
 }
 
-template <int V>
-__global__ void k_upsample(const bf16* __restrict__ x, int xC, int xoff, int C, int H, int W, int B,
-                           bf16* __restrict__ y, int yC, int yoff)
+// Gradient through the nearest upsampling and the ReLU before it, likewise: 2x2 sums of dy
+// (2H x 2W), zero where the upsampled activation a (2H x 2W) is not positive.
+__global__ void __launch_bounds__(256) k_upsample_bwd(const bf16* __restrict__ dy, int dyC, int C, int H, int W, int B,
+                                                      const bf16* __restrict__ a, int aC, bf16* __restrict__ dz, int zC)
 {
-    // x is H x W, y is 2H x 2W
-    const int Ho = 2 * H, Wo = 2 * W, CV = C / V;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= B * Ho * Wo * CV) return;
-    const int c = (k % CV) * V, p = k / CV;
-    const int b = p / (Ho * Wo), r = p - b * Ho * Wo, oy = r / Wo, ox = r - oy * Wo;
-    const bf16* src = x + ((size_t)b * H * W + (oy / 2) * W + ox / 2) * xC + xoff + c;
-    bf16* dst = y + (size_t)p * yC + yoff + c;
-    if constexpr (V == 8) *reinterpret_cast<bf16x8*>(dst) = *reinterpret_cast<const bf16x8*>(src);
-    else dst[0] = src[0];
-}
-
-// Gradient through the nearest upsampling and the ReLU before it: 2x2 sums (dy is 2H x 2W,
-// dz is H x W), zero where the activation a is not positive.
-template <int V>
-__global__ void k_upsample_bwd(const bf16* __restrict__ dy, int dyC, int dyoff, int C, int H, int W,
-                               int B, const bf16* __restrict__ a, int aC, bf16* __restrict__ dz, int zC)
-{
-    const int Wi = 2 * W, CV = C / V;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    const int Wi = 2 * W, CV = C / 8;
+    const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= B * H * W * CV) return;
-    const int c = (k % CV) * V, p = k / CV;
+    const int c = (k % CV) * 8, p = k / CV;
     const int b = p / (H * W), r = p - b * H * W, oy = r / W, ox = r - oy * W;
-    const size_t base = (size_t)b * 4 * H * W;
-    float v00[V], v01[V], v10[V], v11[V], av[V], out[V];
-    load_v<V>(a + (size_t)p * aC + c, av);
-    load_v<V>(dy + (base + (2 * oy) * Wi + 2 * ox) * dyC + dyoff + c, v00);
-    load_v<V>(dy + (base + (2 * oy) * Wi + 2 * ox + 1) * dyC + dyoff + c, v01);
-    load_v<V>(dy + (base + (2 * oy + 1) * Wi + 2 * ox) * dyC + dyoff + c, v10);
-    load_v<V>(dy + (base + (2 * oy + 1) * Wi + 2 * ox + 1) * dyC + dyoff + c, v11);
+    const size_t at = (size_t)b * 4 * H * W + (2 * oy) * Wi + 2 * ox;
+    const bf16x8 m = *reinterpret_cast<const bf16x8*>(a + at * aC + c);
+    bf16x8 v[4], o;
 #pragma unroll
-    for (int i = 0; i < V; ++i) out[i] = av[i] > 0.f ? v00[i] + v01[i] + v10[i] + v11[i] : 0.f;
-    store_v<V>(dz + (size_t)p * zC + c, out);
-}
-
-// dz = (dskip + pool_backward(dpool)) * (a > 0), all at H x W; dpool is H/2 x W/2.
-template <int V>
-__global__ void k_relu_grad(const bf16* __restrict__ dskip, int sC, int soff,
-                            const bf16* __restrict__ dpool, int pC, const bf16* __restrict__ a,
-                            int aC, int aoff, int C, int H, int W, int B, bf16* __restrict__ dz,
-                            int zC)
-{
-    const int CV = C / V;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= B * H * W * CV) return;
-    const int c = (k % CV) * V, p = k / CV;
-    const int b = p / (H * W), r = p - b * H * W, py = r / W, px = r - py * W;
-    const int Wo = W / 2;
-    float g[V], d[V], av[V], out[V];
-    load_v<V>(dskip + (size_t)p * sC + soff + c, g);
-    load_v<V>(dpool + ((size_t)b * (H / 2) * Wo + (py / 2) * Wo + px / 2) * pC + c, d);
+    for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const bf16x8*>(dy + (at + (i >> 1) * Wi + (i & 1)) * dyC + c);
 #pragma unroll
-    for (int i = 0; i < V; ++i) g[i] += 0.25f * d[i];
-    load_v<V>(a + (size_t)p * aC + aoff + c, av);
-#pragma unroll
-    for (int i = 0; i < V; ++i) out[i] = av[i] > 0.f ? g[i] : 0.f;
-    store_v<V>(dz + (size_t)p * zC + c, out);
+    for (int i = 0; i < 8; ++i)
+        o[i] = bf2f(m[i]) > 0.f ? f2bf(bf2f(v[0][i]) + bf2f(v[1][i]) + bf2f(v[2][i]) + bf2f(v[3][i])) : (bf16)0.f;
+    *reinterpret_cast<bf16x8*>(dz + (size_t)p * zC + c) = o;
 }
 
 // Mean squared error: dy = 2 (y - t)/n into a bf16 NHWC buffer (channels padded to whole
@@ -328,10 +256,10 @@ struct clbm_net {
     float* yout;       // network output fp32 NCHW
     bf16* dyout;       // loss gradient (cout padded to whole octets)
     // activations
-    bf16 *a1, *cat1, *p1, *a2, *cat2, *p2, *a3, *cat3, *p3, *a4, *m4, *d3a, *d3b, *d2a, *d2b, *d1a, *d1b;
+    bf16 *a1, *cat1, *p1, *a2, *cat2, *p2, *a3, *cat3, *p3, *a4, *d3a, *d2a, *d1a, *d1b;
     // activation gradients
-    bf16 *g_d1b, *g_d1a, *g_cat1, *g_d2b, *g_d2a, *g_cat2, *g_d3b, *g_d3a, *g_cat3, *g_m4, *g_a4, *g_p3,
-        *g_a3, *g_p2, *g_a2, *g_p1, *g_a1, *g_z;  // g_z: scratch for dz of the current layer
+    bf16 *g_d1b, *g_d1a, *g_cat1, *g_d2b, *g_d2a, *g_cat2, *g_d3b, *g_d3a, *g_cat3, *g_m4, *g_a4,
+        *g_a3, *g_a2, *g_a1, *g_z;  // g_z: scratch for dz of the current layer
     size_t zscratch;
     int weights_stale;
 };
@@ -384,11 +312,8 @@ void layout_net(clbm_net* n, Alloc& a)
     n->cat3 = a.take<bf16>(P3 * (w4 + w3));
     n->p3 = a.take<bf16>(P4 * w3);
     n->a4 = a.take<bf16>(P4 * w4);
-    n->m4 = a.take<bf16>(P4 * w4);
     n->d3a = a.take<bf16>(P3 * w3);
-    n->d3b = a.take<bf16>(P3 * w3);
     n->d2a = a.take<bf16>(P2 * w2);
-    n->d2b = a.take<bf16>(P2 * w2);
     n->d1a = a.take<bf16>(P1 * w1);
     n->d1b = a.take<bf16>(P1 * w1);
     n->yout = a.take<float>(P1 * d.cout);
@@ -405,11 +330,8 @@ void layout_net(clbm_net* n, Alloc& a)
     n->g_cat3 = a.take<bf16>(P3 * (w4 + w3));
     n->g_m4 = a.take<bf16>(P4 * w4);
     n->g_a4 = a.take<bf16>(P4 * w4);
-    n->g_p3 = a.take<bf16>(P4 * w3);
     n->g_a3 = a.take<bf16>(P3 * w3);
-    n->g_p2 = a.take<bf16>(P3 * w2);
     n->g_a2 = a.take<bf16>(P2 * w2);
-    n->g_p1 = a.take<bf16>(P2 * w1);
     n->g_a1 = a.take<bf16>(P1 * w1);
     const size_t zmax = std::max({P1 * (size_t)w1, P2 * (size_t)w2, P3 * (size_t)w3, P4 * (size_t)w4});
     n->zscratch = zmax;
@@ -465,22 +387,19 @@ void layout_net(clbm_net* n, Alloc& a)
     L[4].in = V(n->p2, w2, 0);         L[4].out = V(n->a3, w3, 0);
     L[5].in = V(n->a3, w3, 0);         L[5].out = V(n->cat3, w4 + w3, w4);   // s3
     L[6].in = V(n->p3, w3, 0);         L[6].out = V(n->a4, w4, 0);
-    L[7].in = V(n->a4, w4, 0);         L[7].out = V(n->m4, w4, 0);
+    L[7].in = V(n->a4, w4, 0);
     L[8].in = V(n->cat3, w4 + w3, 0);  L[8].out = V(n->d3a, w3, 0);
-    L[9].in = V(n->d3a, w3, 0);        L[9].out = V(n->d3b, w3, 0);
+    L[9].in = V(n->d3a, w3, 0);
     L[10].in = V(n->cat2, w3 + w2, 0); L[10].out = V(n->d2a, w2, 0);
-    L[11].in = V(n->d2a, w2, 0);       L[11].out = V(n->d2b, w2, 0);
+    L[11].in = V(n->d2a, w2, 0);
     L[12].in = V(n->cat1, w2 + w1, 0); L[12].out = V(n->d1a, w1, 0);
     L[13].in = V(n->d1a, w1, 0);       L[13].out = V(n->d1b, w1, 0);
     L[14].in = V(n->d1b, w1, 0);       L[14].out = V(nullptr, 0, 0);
     // gradient w.r.t. each layer's input
     L[0].din = V(nullptr, 0, 0);
     L[1].din = V(n->g_a1, w1, 0);
-    L[2].din = V(n->g_p1, w1, 0);
     L[3].din = V(n->g_a2, w2, 0);
-    L[4].din = V(n->g_p2, w2, 0);
     L[5].din = V(n->g_a3, w3, 0);
-    L[6].din = V(n->g_p3, w3, 0);
     L[7].din = V(n->g_a4, w4, 0);
     L[8].din = V(n->g_cat3, w4 + w3, 0);
     L[9].din = V(n->g_d3a, w3, 0);
@@ -493,37 +412,35 @@ void layout_net(clbm_net* n, Alloc& a)
 
 dim3 grid1(size_t n, int block = 256) { return dim3((unsigned)((n + block - 1) / block)); }
 
-// True when every channel count, stride and offset allows 8-channel (16-byte) accesses.
-bool vec8(std::initializer_list<int> v)
-{
-    for (int x : v)
-        if (x % 8 != 0) return false;
-    return true;
-}
-
-// Gradient of a decoder level's upsampling (the first C channels of dy, 2H x 2W) through the
-// ReLU of the activations act (H x W).
-clbm_status upsample_bwd(clbm_net* n, TView dy, int C, int H, int W, TView act, TView dz)
+clbm_status pool(clbm_net* n, TView x, int C, int H, int W, TView y)
 {
     const int B = n->d.batch;
-    if (vec8({C, dy.C, dy.off, act.C, dz.C}))
-        hipLaunchKernelGGL(k_upsample_bwd<8>, grid1((size_t)B * H * W * (C / 8)), dim3(256), 0, n->stream,
-                           dy.p, dy.C, dy.off, C, H, W, B, act.p, act.C, dz.p, dz.C);
-    else
-        hipLaunchKernelGGL(k_upsample_bwd<1>, grid1((size_t)B * H * W * C), dim3(256), 0, n->stream,
-                           dy.p, dy.C, dy.off, C, H, W, B, act.p, act.C, dz.p, dz.C);
+    hipLaunchKernelGGL(k_avgpool, grid1((size_t)B * (H / 2) * (W / 2) * (C / 8)), dim3(256), 0, n->stream,
+                       x.p + x.off, x.C, C, H, W, B, y.p + y.off, y.C);
     CLBM_HIP(hipGetLastError());
     return CLBM_OK;
 }
 
-template <int R, int CW, int PX, int PY, int NH>
+// dy and the activations act are 2H x 2W, dz is H x W.
+clbm_status upsample_bwd(clbm_net* n, TView dy, int C, int H, int W, TView act, TView dz)
+{
+    const int B = n->d.batch;
+    hipLaunchKernelGGL(k_upsample_bwd, grid1((size_t)B * H * W * (C / 8)), dim3(256), 0, n->stream, dy.p + dy.off,
+                       dy.C, C, H, W, B, act.p + act.off, act.C, dz.p + dz.off, dz.C);
+    CLBM_HIP(hipGetLastError());
+    return CLBM_OK;
+}
+
+template <int R, int CW, int PX, int PY, int NH, bool POST = false>
 clbm_status launch_rows(clbm_net* n, const ConvArgs& a)
 {
+    if constexpr (NH == 2 && !POST)
+        if (a.post) return launch_rows<R, CW, PX, PY, NH, true>(n, a);
     const int B = a.P / (a.H * a.W);
     const size_t blocks = (size_t)((a.W + 16 * PX - 1) / (16 * PX)) * ((a.H + R * PY - 1) / (R * PY)) * B;
     const dim3 grid((unsigned)blocks, (a.N + 32 * CW - 1) / (32 * CW)), block(64 * CW * PX * PY);
-    if (a.Cin == kKChunk) hipLaunchKernelGGL((k_conv_rows<R, CW, PX, PY, NH, true>), grid, block, 0, n->stream, a);
-    else hipLaunchKernelGGL((k_conv_rows<R, CW, PX, PY, NH, false>), grid, block, 0, n->stream, a);
+    if (a.Cin == kKChunk) hipLaunchKernelGGL((k_conv_rows<R, CW, PX, PY, NH, true, POST>), grid, block, 0, n->stream, a);
+    else hipLaunchKernelGGL((k_conv_rows<R, CW, PX, PY, NH, false, POST>), grid, block, 0, n->stream, a);
     CLBM_HIP(hipGetLastError());
     return CLBM_OK;
 }
@@ -537,18 +454,20 @@ clbm_status launch_taps(clbm_net* n, const ConvArgs& a)
     return CLBM_OK;
 }
 
-template <int R, int CW, int PY, int NH>
+template <int R, int CW, int PY, int NH, bool POST = false>
 clbm_status launch_tile(clbm_net* n, const ConvArgs& a)
 {
+    if constexpr (NH == 2 && !POST)
+        if (a.post) return launch_tile<R, CW, PY, NH, true>(n, a);
     const int B = a.P / (a.H * a.W);
     const size_t blocks = (size_t)((a.W + 15) / 16) * ((a.H + R * PY - 1) / (R * PY)) * B;
     const dim3 grid((unsigned)blocks, (a.N + 32 * CW - 1) / (32 * CW)), block(64 * CW * PY);
     const size_t lds = (size_t)18 * (R * PY + 2) * a.Cin * sizeof(bf16);
     const int nch = a.Cin / kKChunk;
-    if (nch % 4 == 0) hipLaunchKernelGGL((k_conv_tile<R, CW, PY, NH, 4>), grid, block, lds, n->stream, a);
-    else if (nch % 3 == 0) hipLaunchKernelGGL((k_conv_tile<R, CW, PY, NH, 3>), grid, block, lds, n->stream, a);
-    else if (nch % 2 == 0) hipLaunchKernelGGL((k_conv_tile<R, CW, PY, NH, 2>), grid, block, lds, n->stream, a);
-    else hipLaunchKernelGGL((k_conv_tile<R, CW, PY, NH, 1>), grid, block, lds, n->stream, a);
+    if (nch % 4 == 0) hipLaunchKernelGGL((k_conv_tile<R, CW, PY, NH, 4, POST>), grid, block, lds, n->stream, a);
+    else if (nch % 3 == 0) hipLaunchKernelGGL((k_conv_tile<R, CW, PY, NH, 3, POST>), grid, block, lds, n->stream, a);
+    else if (nch % 2 == 0) hipLaunchKernelGGL((k_conv_tile<R, CW, PY, NH, 2, POST>), grid, block, lds, n->stream, a);
+    else hipLaunchKernelGGL((k_conv_tile<R, CW, PY, NH, 1, POST>), grid, block, lds, n->stream, a);
     CLBM_HIP(hipGetLastError());
     return CLBM_OK;
 }
@@ -562,8 +481,16 @@ bool chunk_order(int H, int W)
     return (bw == 64 || bw == 32 || bw == 16) && W % bw == 0 && H % (256 / bw) == 0;
 }
 
-clbm_status conv_launch(clbm_net* n, const Layer& l, TView in, int cin_pad, const bf16* w,
-                        const float* bias, int N, int mode, TView out, float* yf, TView mask = TView{nullptr, 0, 0})
+struct Post {
+    int kind;        // ConvPost
+    TView e, e2;
+    int n;
+};
+constexpr TView kNoView{nullptr, 0, 0};
+constexpr Post kNoPost{kPostNone, kNoView, kNoView, 0};
+
+clbm_status conv_launch(clbm_net* n, const Layer& l, TView in, int cin_pad, const bf16* w, const float* bias, int N,
+                        int mode, TView out, float* yf, float* yf2, TView mask, const Post& post)
 {
     ConvArgs a;
     a.x = in.p;
@@ -584,6 +511,23 @@ clbm_status conv_launch(clbm_net* n, const Layer& l, TView in, int cin_pad, cons
     a.yf = yf;
     a.mask = mask.p ? mask.p + mask.off : nullptr;
     a.maskC = mask.C;
+    a.yf2 = yf2;
+    a.post = post.kind;
+    a.e = post.e.p ? post.e.p + post.e.off : nullptr;
+    a.eC = post.e.C;
+    a.eN = post.n;
+    a.e2 = post.e2.p ? post.e2.p + post.e2.off : nullptr;
+    a.e2C = post.e2.C;
+    // 16-pixel waves hold no 2 x 2 pixels
+    auto taps = [&](bool big) {
+        const int kind = a.post;
+        if (kind == kPostPool || kind == kPostSum) a.post = kPostNone;
+        if (kind == kPostSum) a.mask = nullptr;
+        const clbm_status st = big && !a.post ? launch_taps<4, 2>(n, a) : launch_taps<1, 2>(n, a);
+        if (st == CLBM_OK && kind == kPostPool) return pool(n, out, N, l.H, l.W, post.e);
+        if (st == CLBM_OK && kind == kPostSum) return upsample_bwd(n, out, post.n, l.H / 2, l.W / 2, mask, post.e);
+        return st;
+    };
     const bool one = cin_pad == kKChunk;
     if (mode == 2) {
         // the output layer: at most 16 channels, in one group; the first four need one row block
@@ -608,14 +552,13 @@ clbm_status conv_launch(clbm_net* n, const Layer& l, TView in, int cin_pad, cons
     // 32 x 32 images, all six layers at 8 x 8 and 4 x 4: 73 us against 78 us; 16 images of
     // 24 x 20 (768 waves) already take 17.5 against 13.7 us.
     const size_t tile_waves = (size_t)((a.W + 15) / 16) * ((a.H + 3) / 4) * (a.P / (a.H * a.W)) * groups;
-    if (tile_waves < 512) return launch_taps<1, 2>(n, a);
+    if (tile_waves < 512) return taps(false);
     // tiles of four rows per wave, 18 x 6 (one wave down) or 18 x 10 (two) pixels with the halo,
     // within the 160 KB of LDS
     if (groups % 4 == 0 && 18 * 6 * a.Cin * 2 <= 160 * 1024) return launch_tile<4, 4, 1, 2>(n, a);
     if (groups % 2 == 0 && 18 * 10 * a.Cin * 2 <= 160 * 1024) return launch_tile<4, 2, 2, 2>(n, a);
     if (18 * 10 * a.Cin * 2 <= 160 * 1024) return launch_tile<4, 1, 2, 2>(n, a);
-    if ((size_t)a.P / 64 * groups >= 2048) return launch_taps<4, 2>(n, a);
-    return launch_taps<1, 2>(n, a);
+    return taps((size_t)a.P / 64 * groups >= 2048);
 }
 
 clbm_status prep_weights(clbm_net* n)
@@ -643,32 +586,6 @@ clbm_status prep_weights(clbm_net* n)
     CLBM_HIP(hipGetLastError());
     n->weights_stale = 0;
     return CLBM_OK;
-}
-
-clbm_status ew_launch_check() { CLBM_HIP(hipGetLastError()); return CLBM_OK; }
-
-clbm_status pool(clbm_net* n, TView x, int C, int H, int W, TView y)
-{
-    const int B = n->d.batch;
-    if (vec8({C, x.C, x.off, y.C, y.off}))
-        hipLaunchKernelGGL(k_avgpool<8>, grid1((size_t)B * (H / 2) * (W / 2) * (C / 8)), dim3(256), 0,
-                           n->stream, x.p, x.C, x.off, C, H, W, B, y.p, y.C, y.off);
-    else
-        hipLaunchKernelGGL(k_avgpool<1>, grid1((size_t)B * (H / 2) * (W / 2) * C), dim3(256), 0, n->stream,
-                           x.p, x.C, x.off, C, H, W, B, y.p, y.C, y.off);
-    return ew_launch_check();
-}
-
-clbm_status upsample(clbm_net* n, TView x, int C, int H, int W, TView y)
-{
-    const int B = n->d.batch;
-    if (vec8({C, x.C, x.off, y.C, y.off}))
-        hipLaunchKernelGGL(k_upsample<8>, grid1((size_t)B * 4 * H * W * (C / 8)), dim3(256), 0, n->stream,
-                           x.p, x.C, x.off, C, H, W, B, y.p, y.C, y.off);
-    else
-        hipLaunchKernelGGL(k_upsample<1>, grid1((size_t)B * 4 * H * W * C), dim3(256), 0, n->stream, x.p,
-                           x.C, x.off, C, H, W, B, y.p, y.C, y.off);
-    return ew_launch_check();
 }
 
 template <int NA, int RING, bool WIDE>
@@ -733,30 +650,14 @@ clbm_status wgrad_launch(clbm_net* n, const Layer& l, TView dz)
 // Backward through one convolution: dz (gradient w.r.t. its output pre-activation,
 // ReLU already applied) -> weight and bias gradients, and the input gradient when the
 // layer has one, taken through the ReLU of the activations `mask` where that is given.
-clbm_status conv_backward(clbm_net* n, int k, TView dz, TView mask = TView{nullptr, 0, 0})
+clbm_status conv_backward(clbm_net* n, int k, TView dz, TView mask = kNoView, const Post& post = kNoPost)
 {
     const Layer& l = n->L[k];
     const clbm_status st = l.cout_kpad % 64 == 0 ? wgrad_launch<4>(n, l, dz) : wgrad_launch<2>(n, l, dz);
     if (st != CLBM_OK) return st;
     // input gradient: convolution of dz with the flipped, transposed kernel
-    if (l.din.p) {
-        return conv_launch(n, l, dz, l.cout_kpad, l.wb, nullptr, l.cin, 1, l.din, nullptr, mask);
-    }
-    return CLBM_OK;
-}
-
-clbm_status relu_grad(clbm_net* n, TView dy, TView dpool_parent, TView act, int C, int H, int W, TView dz)
-{
-    const int B = n->d.batch;
-    if (vec8({C, dy.C, dy.off, dpool_parent.C, act.C, act.off, dz.C}))
-        hipLaunchKernelGGL(k_relu_grad<8>, grid1((size_t)B * H * W * (C / 8)), dim3(256), 0, n->stream,
-                           dy.p, dy.C, dy.off, dpool_parent.p, dpool_parent.C, act.p, act.C, act.off, C,
-                           H, W, B, dz.p, dz.C);
-    else
-        hipLaunchKernelGGL(k_relu_grad<1>, grid1((size_t)B * H * W * C), dim3(256), 0, n->stream, dy.p,
-                           dy.C, dy.off, dpool_parent.p, dpool_parent.C, act.p, act.C, act.off, C, H,
-                           W, B, dz.p, dz.C);
-    return ew_launch_check();
+    if (k == 0) return CLBM_OK;
+    return conv_launch(n, l, dz, l.cout_kpad, l.wb, nullptr, l.cin, 1, l.din, nullptr, nullptr, mask, post);
 }
 
 }  // namespace
@@ -861,28 +762,20 @@ clbm_status clbm_net_forward(clbm_net* n, const float* d_x, float* d_y)
                        H * W, B * H * W, n->xin, cinp);
     CLBM_HIP(hipGetLastError());
     Layer* L = n->L;
-    auto fwd = [&](int k) {
+    auto fwd = [&](int k, const Post& post = kNoPost) {
         const Layer& l = L[k];
         return conv_launch(n, l, l.in, l.cin_pad, l.wf, n->params + l.boff, l.cout, k == 14 ? 2 : 0, l.out,
-                           k == 14 ? n->yout : nullptr);
+                           k == 14 ? n->yout : nullptr, k == 14 ? d_y : nullptr, kNoView, post);
     };
-    auto V = [](bf16* p, int C, int off) { return TView{p, C, off}; };
-    if ((st = fwd(0)) || (st = fwd(1))) return st;
-    if ((st = pool(n, V(n->cat1, w2 + w1, w2), w1, H, W, V(n->p1, w1, 0)))) return st;
-    if ((st = fwd(2)) || (st = fwd(3))) return st;
-    if ((st = pool(n, V(n->cat2, w3 + w2, w3), w2, H / 2, W / 2, V(n->p2, w2, 0)))) return st;
-    if ((st = fwd(4)) || (st = fwd(5))) return st;
-    if ((st = pool(n, V(n->cat3, w4 + w3, w4), w3, H / 4, W / 4, V(n->p3, w3, 0)))) return st;
-    if ((st = fwd(6)) || (st = fwd(7))) return st;
-    if ((st = upsample(n, V(n->m4, w4, 0), w4, H / 8, W / 8, V(n->cat3, w4 + w3, 0)))) return st;
-    if ((st = fwd(8)) || (st = fwd(9))) return st;
-    if ((st = upsample(n, V(n->d3b, w3, 0), w3, H / 4, W / 4, V(n->cat2, w3 + w2, 0)))) return st;
-    if ((st = fwd(10)) || (st = fwd(11))) return st;
-    if ((st = upsample(n, V(n->d2b, w2, 0), w2, H / 2, W / 2, V(n->cat1, w2 + w1, 0)))) return st;
+    auto pooled = [&](bf16* p, int C) { return Post{kPostPool, TView{p, C, 0}, kNoView, 0}; };
+    auto up = [&](bf16* p, int C) { return Post{kPostUp, TView{p, C, 0}, kNoView, 0}; };
+    if ((st = fwd(0)) || (st = fwd(1, pooled(n->p1, w1)))) return st;
+    if ((st = fwd(2)) || (st = fwd(3, pooled(n->p2, w2)))) return st;
+    if ((st = fwd(4)) || (st = fwd(5, pooled(n->p3, w3)))) return st;
+    if ((st = fwd(6)) || (st = fwd(7, up(n->cat3, w4 + w3)))) return st;
+    if ((st = fwd(8)) || (st = fwd(9, up(n->cat2, w3 + w2)))) return st;
+    if ((st = fwd(10)) || (st = fwd(11, up(n->cat1, w2 + w1)))) return st;
     if ((st = fwd(12)) || (st = fwd(13)) || (st = fwd(14))) return st;
-    if (d_y)
-        CLBM_HIP(hipMemcpyAsync(d_y, n->yout, (size_t)B * d.cout * H * W * sizeof(float),
-                                hipMemcpyDeviceToDevice, n->stream));
     return CLBM_OK;
 }
 
@@ -906,33 +799,25 @@ clbm_status clbm_net_backward(clbm_net* n, const float* d_target, double* loss)
     // output layer (no activation); each input gradient leaves its convolution as the gradient
     // before the ReLU of the layer below
     if ((st = conv_backward(n, 14, V(n->dyout, coutp, 0), V(n->d1b, w1, 0)))) return st;
-    // level-1 decoder
+    // decoder; the gradient of [up | skip] leaves the upsampled part as the gradient of the level
+    // below, the skip's for the encoder
+    auto sum = [&](bf16* dz, int C) { return Post{kPostSum, V(dz, C, 0), kNoView, C}; };
+    auto cat = [&](bf16* p, int up, int skip) { return V(p, up + skip, 0); };
     if ((st = conv_backward(n, 13, V(n->g_d1b, w1, 0), V(n->d1a, w1, 0)))) return st;
-    if ((st = conv_backward(n, 12, V(n->g_d1a, w1, 0)))) return st;
-    // g_cat1 = [d up(d2b) | d s1]
-    if ((st = upsample_bwd(n, V(n->g_cat1, w2 + w1, 0), w2, H / 2, W / 2, V(n->d2b, w2, 0), V(n->g_d2b, w2, 0)))) return st;
-    // level-2 decoder
+    if ((st = conv_backward(n, 12, V(n->g_d1a, w1, 0), cat(n->cat1, w2, w1), sum(n->g_d2b, w2)))) return st;
     if ((st = conv_backward(n, 11, V(n->g_d2b, w2, 0), V(n->d2a, w2, 0)))) return st;
-    if ((st = conv_backward(n, 10, V(n->g_d2a, w2, 0)))) return st;
-    if ((st = upsample_bwd(n, V(n->g_cat2, w3 + w2, 0), w3, H / 4, W / 4, V(n->d3b, w3, 0), V(n->g_d3b, w3, 0)))) return st;
-    // level-3 decoder
+    if ((st = conv_backward(n, 10, V(n->g_d2a, w2, 0), cat(n->cat2, w3, w2), sum(n->g_d3b, w3)))) return st;
     if ((st = conv_backward(n, 9, V(n->g_d3b, w3, 0), V(n->d3a, w3, 0)))) return st;
-    if ((st = conv_backward(n, 8, V(n->g_d3a, w3, 0)))) return st;
-    if ((st = upsample_bwd(n, V(n->g_cat3, w4 + w3, 0), w4, H / 8, W / 8, V(n->m4, w4, 0), V(n->g_m4, w4, 0)))) return st;
+    if ((st = conv_backward(n, 8, V(n->g_d3a, w3, 0), cat(n->cat3, w4, w3), sum(n->g_m4, w4)))) return st;
     // bottom level
     if ((st = conv_backward(n, 7, V(n->g_m4, w4, 0), V(n->a4, w4, 0)))) return st;
-    if ((st = conv_backward(n, 6, V(n->g_a4, w4, 0)))) return st;
-    // encoder: skip gradient + pooled gradient, through the ReLU
-    if ((st = relu_grad(n, V(n->g_cat3, w4 + w3, w4), V(n->g_p3, w3, 0), V(n->cat3, w4 + w3, w4), w3,
-                        H / 4, W / 4, zv(w3)))) return st;
+    // encoder: the pooled activations' gradient, with the skip's and through the ReLU to g_z
+    auto unpool = [&](bf16* skip, int up, int C) { return Post{kPostUnpool, zv(C), V(skip, up + C, up), 0}; };
+    if ((st = conv_backward(n, 6, V(n->g_a4, w4, 0), V(n->cat3, w4 + w3, w4), unpool(n->g_cat3, w4, w3)))) return st;
     if ((st = conv_backward(n, 5, zv(w3), V(n->a3, w3, 0)))) return st;
-    if ((st = conv_backward(n, 4, V(n->g_a3, w3, 0)))) return st;
-    if ((st = relu_grad(n, V(n->g_cat2, w3 + w2, w3), V(n->g_p2, w2, 0), V(n->cat2, w3 + w2, w3), w2,
-                        H / 2, W / 2, zv(w2)))) return st;
+    if ((st = conv_backward(n, 4, V(n->g_a3, w3, 0), V(n->cat2, w3 + w2, w3), unpool(n->g_cat2, w3, w2)))) return st;
     if ((st = conv_backward(n, 3, zv(w2), V(n->a2, w2, 0)))) return st;
-    if ((st = conv_backward(n, 2, V(n->g_a2, w2, 0)))) return st;
-    if ((st = relu_grad(n, V(n->g_cat1, w2 + w1, w2), V(n->g_p1, w1, 0), V(n->cat1, w2 + w1, w2), w1, H,
-                        W, zv(w1)))) return st;
+    if ((st = conv_backward(n, 2, V(n->g_a2, w2, 0), V(n->cat1, w2 + w1, w2), unpool(n->g_cat1, w2, w1)))) return st;
     if ((st = conv_backward(n, 1, zv(w1), V(n->a1, w1, 0)))) return st;
     if ((st = conv_backward(n, 0, V(n->g_a1, w1, 0)))) return st;
     if (loss) {
