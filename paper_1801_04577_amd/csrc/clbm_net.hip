@@ -162,21 +162,39 @@ struct FieldAffine {
     float scale[16], shift[16];
 };
 
-__global__ void k_resample(const float* __restrict__ src, int sh, int sw, float* __restrict__ dst,
-                           int dh, int dw, int nf, FieldAffine af)
+// A thread takes V neighbouring cells of one field: one row for all of them, one store. Bound
+// by its launch and one chain of loads: 32 lattices of three fields 128^2 onto 512^2 take 127 us,
+// 160 with a cell per thread.
+template <int V>
+__global__ void __launch_bounds__(256) k_resample(const float* __restrict__ src, int sh, int sw, float* __restrict__ dst,
+                                                  int dh, int dw, FieldAffine af)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nf * dh * dw) return;
-    const int f = k / (dh * dw), r = k - f * dh * dw, y = r / dw, x = r - y * dw;
+    const int per = dw / V, k = blockIdx.x * 256 + threadIdx.x, f = blockIdx.y;
+    if (k >= dh * per) return;
+    const int y = k / per, x = (k - y * per) * V;
     const float fy = fminf(fmaxf((y + 0.5f) * sh / dh - 0.5f, 0.f), (float)(sh - 1));
-    const float fx = fminf(fmaxf((x + 0.5f) * sw / dw - 0.5f, 0.f), (float)(sw - 1));
-    const int y0 = (int)fy, x0 = (int)fx;
-    const int y1 = min(y0 + 1, sh - 1), x1 = min(x0 + 1, sw - 1);
-    const float ty = fy - y0, tx = fx - x0;
+    const int y0 = (int)fy, y1 = min(y0 + 1, sh - 1);
+    const float ty = fy - y0;
+    int x0[V], x1[V];
+    float tx[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const float fx = fminf(fmaxf((x + i + 0.5f) * sw / dw - 0.5f, 0.f), (float)(sw - 1));
+        x0[i] = (int)fx;
+        x1[i] = min(x0[i] + 1, sw - 1);
+        tx[i] = fx - x0[i];
+    }
     const float* s = src + (size_t)f * sh * sw;
-    const float v = (1.f - ty) * ((1.f - tx) * s[y0 * sw + x0] + tx * s[y0 * sw + x1]) +
-                    ty * ((1.f - tx) * s[y1 * sw + x0] + tx * s[y1 * sw + x1]);
-    dst[k] = af.scale[f] * v + af.shift[f];
+    float o[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const float v = (1.f - ty) * ((1.f - tx[i]) * s[y0 * sw + x0[i]] + tx[i] * s[y0 * sw + x1[i]]) +
+                        ty * ((1.f - tx[i]) * s[y1 * sw + x0[i]] + tx[i] * s[y1 * sw + x1[i]]);
+        o[i] = af.scale[f] * v + af.shift[f];
+    }
+    float* to = dst + ((size_t)f * dh + y) * dw + x;
+    if constexpr (V == 4) *reinterpret_cast<f32x4*>(to) = f32x4{o[0], o[1], o[2], o[3]};
+    else to[0] = o[0];
 }
 
 // Input planes of the warm-start network for one problem per sample (see
@@ -579,10 +597,9 @@ clbm_status prep_weights(clbm_net* n)
         p.chunks_f = l.cin_pad / kKChunk;
         p.chunks_b = l.cout_kpad / kKChunk;
         p.first = t.total;
-        p.lanes_f = l.cout_kpad / 32 * p.chunks_f * 9 * 128;
-        t.total += p.lanes_f * (l.wb ? 2 : 1);
+        t.total += l.cout_kpad / 32 * p.chunks_f;
     }
-    hipLaunchKernelGGL(k_weight_prep, grid1((size_t)t.total), dim3(256), 0, n->stream, n->params, t);
+    hipLaunchKernelGGL(k_weight_prep, dim3(t.total), dim3(256), 0, n->stream, n->params, t);
     CLBM_HIP(hipGetLastError());
     n->weights_stale = 0;
     return CLBM_OK;
@@ -851,8 +868,12 @@ clbm_status clbm_resample_bilinear(const float* d_src, int sh, int sw, float* d_
         af.scale[f] = (scale && f < nfields) ? scale[f] : 1.f;
         af.shift[f] = (shift && f < nfields) ? shift[f] : 0.f;
     }
-    hipLaunchKernelGGL(k_resample, grid1((size_t)nfields * dh * dw), dim3(256), 0, (hipStream_t)hip_stream,
-                       d_src, sh, sw, d_dst, dh, dw, nfields, af);
+    if (dw % 4 == 0 && (uintptr_t)d_dst % 16 == 0)
+        hipLaunchKernelGGL(k_resample<4>, dim3(grid1((size_t)dh * (dw / 4)).x, nfields), dim3(256), 0, (hipStream_t)hip_stream,
+                           d_src, sh, sw, d_dst, dh, dw, af);
+    else
+        hipLaunchKernelGGL(k_resample<1>, dim3(grid1((size_t)dh * dw).x, nfields), dim3(256), 0, (hipStream_t)hip_stream,
+                           d_src, sh, sw, d_dst, dh, dw, af);
     CLBM_HIP(hipGetLastError());
     return CLBM_OK;
 }

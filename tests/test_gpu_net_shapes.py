@@ -53,3 +53,28 @@ def test_shapes_elementwise(B, H, W, cin, cout, widths):
     print("worst %.3f of the unit" % max(ratios), flush=True)
     assert loss == pytest.approx(want_loss, rel=1e-3)
     assert max(ratios) <= 4.0
+
+
+@pytest.mark.parametrize("sh,sw,dh,dw,nf", [(5, 7, 3, 4, 1), (16, 12, 33, 20, 3), (9, 9, 21, 30, 2), (128, 64, 96, 7, 16)])
+def test_resample_widths(sh, sw, dh, dw, nf):
+    """Rows that are and are not a multiple of four cells, against 64 bits. A coordinate is off by
+    at most four roundings of its size, which moves a value by at most twice the fields' largest
+    times that; the sum of four products and the affine map add eight roundings."""
+    import torch
+    import paper_1801_04577_amd as clbm
+    src = np.random.default_rng(dw).normal(size=(nf, sh, sw)).astype(np.float32)
+    scale, shift = [1.0 + 0.5 * f for f in range(nf)], [0.25 * f for f in range(nf)]
+    got = clbm.resample(torch.from_numpy(src).cuda(), dh, dw, scale=scale, shift=shift).cpu().numpy().astype(np.float64)
+
+    def axis(n, m):
+        f = np.clip((np.arange(m) + 0.5) * n / m - 0.5, 0, n - 1)
+        lo = f.astype(int)
+        return lo, np.minimum(lo + 1, n - 1), f - lo
+    y0, y1, ty = axis(sh, dh)
+    x0, x1, tx = axis(sw, dw)
+    s = src.astype(np.float64)
+    rows = s[:, y0] * (1 - ty)[None, :, None] + s[:, y1] * ty[None, :, None]
+    want = rows[:, :, x0] * (1 - tx) + rows[:, :, x1] * tx
+    want = want * np.array(scale)[:, None, None] + np.array(shift)[:, None, None]
+    big = np.abs(s).max() * max(scale) + max(shift)
+    assert np.abs(got - want).max() <= 2.0 ** -24 * (8 + 8 * (sh + sw)) * big
