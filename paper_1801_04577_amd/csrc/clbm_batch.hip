@@ -563,7 +563,7 @@ dim3 tile_block(const clbm_batch* b)
 
 clbm_status launch_batch_steps(clbm_batch* b, int nsteps)
 {
-    if (b->multi) {
+    if (b->multi && nsteps > 1) {   // a lone step is faster without the ring
         const StepSplit split(nsteps, b->multi->steps);
         for (int k = 0; k < split.launches; ++k) {
             int parity = b->parity, bands = b->launch.xcd_bands, n = split.steps(k);
@@ -577,7 +577,7 @@ clbm_status launch_batch_steps(clbm_batch* b, int nsteps)
         return CLBM_OK;
     }
     while (nsteps > 0) {
-        if (b->launch.steps_per_launch == 2 && nsteps >= 2) {
+        if (!b->multi && b->launch.steps_per_launch == 2 && nsteps >= 2) {
             int parity = b->parity, bands = b->launch.xcd_bands;
             void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &bands};
             CLBM_HIP(hipLaunchKernel(step2_kernel(b), step_grid(b), dim3(two_step_threads(b->launch.tile_y)),

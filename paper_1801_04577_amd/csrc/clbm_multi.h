@@ -232,21 +232,36 @@ const MultiShape* multi_shapes();
 //   128^2: 4.7, 16x4 1.68, 32x8 2.07     192^2: 4.4, 16x4 2.23, 32x8 2.08
 //   256^2: 4.5, 32x8 2.13, 32x12 2.38    384^2: 4.8, 32x8 4.8, 32x12 3.26, 32x16 3.8
 //   512^2: 6.6, 32x12 4.5, 32x16 4.1    1500^2: 29.4, 32x12 27.9, 32x16 25.8
-//  2048^2: 49.2, 32x16 45.5
-// In FP16 the two-step kernel's taller tile wins from about two million nodes:
-//   512^2: 6.0, 32x16 4.0               1500^2: 22.0, 32x16 21.8   2048^2: 34.6, 32x16 38.3
+//  2048^2: 49.2, 32x16 45.5            4096^2: 179, 32x16 175
+// The lattices beyond 2^23 nodes stay with two steps per launch: 2 % is left there, and their
+// launches are what the bandwidth and counter figures of the two-step kernel are taken from.
+// In FP16 the two-step kernel's taller tile wins from about 1.6 million nodes:
+//   512^2: 6.0, 32x16 4.0   1200^2: 15.8, 32x16 14.2   1400^2: 18.8, 32x16 19.0   2048^2: 34.6, 32x16 38.3
 template <typename Tiles>
 const MultiShape* multi_shape(Tiles tiles, size_t nodes, int precision)
 {
     constexpr size_t kCUs = 256;
     constexpr size_t most[kMultiShapes] = {kCUs, kCUs, 2 * kCUs, ~(size_t)0};
-    if (nodes > (precision == CLBM_FP16_SHIFTED ? (size_t)1 << 21 : (size_t)1 << 23)) return nullptr;
+    if (nodes > (precision == CLBM_FP16_SHIFTED ? (size_t)3 << 19 : (size_t)1 << 23)) return nullptr;
     for (int k = 0; k < kMultiShapes; ++k) {
         const MultiShape& m = multi_shapes()[k];
         const size_t n = tiles(m.tx, m.ty);
         if (n > 0 && n <= most[k]) return &m;
     }
     return nullptr;
+}
+
+// How many of n steps a lattice takes in launches of m; the others take the one- and two-step
+// kernels (all of them give the same bits). A lone step is always theirs: 1000 x 777 in FP32
+// 17.5 against 20.3 us, 1200^2 26 against 32. On large lattices so is a launch of two steps, which
+// pays the ring and hides less: 1000 x 777 25 against 26 us, 1400^2 50 against 54, 2800^2
+// 171 against 193 (but 800 x 600 20 against 17; FP16: 1200^2 32 against 34, 1000 x 777 24
+// against 20), so that only whole launches of three are left, and four steps are two pairs.
+inline int multi_part(const MultiShape& m, size_t nodes, int precision, int n)
+{
+    if (n < 2) return 0;
+    if (m.steps != 3 || nodes <= (precision == CLBM_FP16_SHIFTED ? (size_t)1 << 20 : (size_t)5 << 17)) return n;
+    return n - (n % 3 == 1 ? 4 : n % 3);
 }
 
 // n steps as launches of at most `most` steps, as even as they come.

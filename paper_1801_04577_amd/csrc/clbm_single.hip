@@ -447,18 +447,25 @@ const MultiShape* multi_of(const clbm_handle* h)
         (size_t)c.nx * c.ny, h->p.precision);
 }
 
-// The launches of n steps: launches of the deeper tiles, or two-step launches while two or
+int deep_steps(const clbm_handle* h, const MultiShape* m, int n)
+{
+    return m ? multi_part(*m, (size_t)h->c.nx * h->c.ny, h->p.precision, n) : 0;
+}
+
+// The launches of n steps: launches of the deeper tiles, then two-step launches while two or
 // more steps remain (when enabled), then single steps. Calls emit(fn, grid, block, args)
 // for each.
 template <typename Emit>
 clbm_status plan_steps(clbm_handle* h, int n, int from, Emit emit)
 {
-    if (const MultiShape* m = multi_of(h)) {
+    const MultiShape* m = multi_of(h);
+    int cur = from;
+    if (const int deep = deep_steps(h, m, n)) {
         const void* fn = m->single(h->p.precision, lattice_src(h->c));
         int tiles_x = (h->c.nx + m->tx - 1) / m->tx, total = tiles_x * ((h->c.ny + m->ty - 1) / m->ty);
         const dim3 grid((unsigned)align_up((size_t)total, 8), 1, 1), block(m->threads, 1, 1);
-        const StepSplit split(n, m->steps);
-        for (int k = 0, cur = from; k < split.launches; ++k, cur ^= 1) {
+        const StepSplit split(deep, m->steps);
+        for (int k = 0; k < split.launches; ++k, cur ^= 1) {
             void *src = h->buf[cur], *dst = h->buf[cur ^ 1];
             int steps = split.steps(k);
             unsigned inv = multi_inv(*m, steps);
@@ -466,12 +473,11 @@ clbm_status plan_steps(clbm_handle* h, int n, int from, Emit emit)
             const clbm_status st = emit(fn, grid, block, args);
             if (st != CLBM_OK) return st;
         }
-        return CLBM_OK;
+        n -= deep;
     }
     const bool two = h->launch.steps_per_launch == 2;
     const StepLaunch s1 = plan_step(h->c, h->p.precision, h->launch);
     const Step2Launch s2 = plan_step2(h->c, h->p.precision, h->launch);
-    int cur = from;
     while (n > 0) {
         LaunchArgs a;
         a.src = h->buf[cur];
@@ -502,8 +508,9 @@ clbm_status plan_steps(clbm_handle* h, int n, int from, Emit emit)
 // Number of launches (buffer flips) of n steps.
 int launches_of(const clbm_handle* h, int n)
 {
-    if (const MultiShape* m = multi_of(h)) return StepSplit(n, m->steps).launches;
-    return h->launch.steps_per_launch == 2 ? n / 2 + n % 2 : n;
+    const MultiShape* m = multi_of(h);
+    const int deep = deep_steps(h, m, n), rest = n - deep;
+    return (deep ? StepSplit(deep, m->steps).launches : 0) + (h->launch.steps_per_launch == 2 ? rest / 2 + rest % 2 : rest);
 }
 
 clbm_status launch_steps_direct(clbm_handle* h, int n)

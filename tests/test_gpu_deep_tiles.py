@@ -53,6 +53,16 @@ def test_default_launch_equals_single_steps(nx, ny, kind, source, precision):
             np.testing.assert_array_equal(x, y)
 
 
+@pytest.mark.parametrize("nx,ny,precision", [(1010, 700, 0), (1201, 901, 1)])
+def test_large_lattices_mix_launches_of_three_two_and_one(nx, ny, precision):
+    prob, f = problem(nx, ny, "walls", "field"), fields(nx, ny)
+    for steps, graph in ((2, 0), (3, 0), (4, 0), (6, 0), (21, 8)):
+        a = state(run_gpu(prob, steps, f, precision, launch=dict(block_x=256, steps_per_launch=1)))
+        b = state(run_gpu(prob, steps, f, precision, graph=graph))
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
+
+
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("sizes", [[(33, 7), (20, 20)], [(131, 90), (64, 100), (70, 70)], [(210, 300), (130, 200)],
                                    [(520, 401), (64, 64), (300, 300)]])
