@@ -110,8 +110,8 @@ typedef struct {
  * (rounded into the storage type exactly as a stored state) by workgroups that own tiles
  * of 64 x two_step_rows nodes: two_step_rows 6, 14, 22 or 30 (256, 512, 512 or 1024
  * threads). 0 leaves the tiles to the library: lattices of up to 8 million nodes (FP32) or
- * 2 million (FP16) take smaller tiles with up to six steps per launch, larger ones 64 x 14
- * (FP32) or 64 x 22 (FP16) with two;
+ * 1.5 million (FP16) take smaller tiles with up to six steps per launch (a lone step and
+ * what is left of a call by itself), larger ones 64 x 14 (FP32) or 64 x 22 (FP16) with two;
  * xcd_remap applies to the two-step tiles too, the other fields shape only the single step that
  * ends an odd step count (256 x 1 threads, one row each, if they do not form a valid
  * shape). All of them give bitwise identical states.
@@ -268,7 +268,7 @@ enum { CLBM_INST_RUNNING = 0, CLBM_INST_CONVERGED = 1, CLBM_INST_DIVERGED = 2,
  * (launch NULL at create) is the two-step 64 x 14 shape, one workgroup per tile, in XCD
  * bands; with exactly that launch the library takes smaller tiles and up to six steps per
  * launch where the instances together hold no more than 8 million nodes (FP32) or
- * 2 million (FP16), with the same states bit for bit. */
+ * 1.5 million (FP16), with the same states bit for bit. */
 typedef struct {
     int tile_x, tile_y, persistent_wgs;
     int steps_per_launch;
