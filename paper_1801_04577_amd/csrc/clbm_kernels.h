@@ -169,19 +169,26 @@ __device__ __forceinline__ void gather_mem(const Mem& mem, const LatticeConst& c
         // Eq. (26): g_i(x_f, t+1) = -g*_opp(i)(x_f, t) + c_T^2 T_w, with T_w from Eq. (28)
         // using T at this node (T1) and one node further from the wall (T2) at time t.
         // Post-collision data give T = sum g* - Q/2 (the collision adds Q).
-        // T1 and both T2 (along x and along y; the node itself where it has no wall there)
-        // are loaded before the first is used, so a wall node waits for memory once.
         auto theta = [&](Off off, int qx, int qy) {
             return theta_at<SRC, typename Mem::Elem, P>(src, c, off, node_q<SRC>(c, qx, qy));
         };
-        const int dx = oxm ? 1 : (oxp ? -1 : 0), dy = oym ? 1 : (oyp ? -1 : 0);
         const float th1 = theta(own, x, y);
-        const float thx = theta(rC + (dx ? mem.col(x, dx) : cC), x + dx, y);
-        const float thy = theta((dy ? mem.row(y, dy) : rC) + cC, x, y + dy);
-        if (oxm) b[1] = -b[1] + CT2 * (c.a1[0] * th1 + c.a2[0] * thx + c.a3[0]);
-        if (oxp) b[3] = -b[3] + CT2 * (c.a1[1] * th1 + c.a2[1] * thx + c.a3[1]);
-        if (oym) b[2] = -b[2] + CT2 * (c.a1[2] * th1 + c.a2[2] * thy + c.a3[2]);
-        if (oyp) b[4] = -b[4] + CT2 * (c.a1[3] * th1 + c.a2[3] * thy + c.a3[3]);
+        if (oxm) {
+            const float tw = c.a1[0] * th1 + c.a2[0] * theta(rC + mem.col(x, 1), x + 1, y) + c.a3[0];
+            b[1] = -b[1] + CT2 * tw;
+        }
+        if (oxp) {
+            const float tw = c.a1[1] * th1 + c.a2[1] * theta(rC + mem.col(x, -1), x - 1, y) + c.a3[1];
+            b[3] = -b[3] + CT2 * tw;
+        }
+        if (oym) {
+            const float tw = c.a1[2] * th1 + c.a2[2] * theta(mem.row(y, 1) + cC, x, y + 1) + c.a3[2];
+            b[2] = -b[2] + CT2 * tw;
+        }
+        if (oyp) {
+            const float tw = c.a1[3] * th1 + c.a2[3] * theta(mem.row(y, -1) + cC, x, y - 1) + c.a3[3];
+            b[4] = -b[4] + CT2 * tw;
+        }
         if (c.moving) add_wall_motion(c, src + own, P, oxm, oxp, oym, oyp, a);
     }
 }
