@@ -27,9 +27,6 @@ constexpr int kChunkW = 18 * kFrag;  // weights of 32 channels over a chunk: 9 t
 __device__ __forceinline__ float bf2f(bf16 v) { return (float)v; }
 __device__ __forceinline__ bf16 f2bf(float v) { return (bf16)v; }
 
-// Weights of one direction of a layer as its convolution reads them: per group of 32 output
-// channels, chunk of 32 input channels and tap (in the order they are accumulated) and row
-// block h one fragment of 1 KB, lane after lane. Row i of block h is channel 8 (i/4) + 4 h + i % 4 of the group.
 // What an epilogue does besides (kPostPool) or instead of writing its output: everything that the
 // network does between two convolutions, on values still in registers and rounded to bf16
 // as they would have been stored. Pool and Sum need 2 x 2 pixels in one wave: rows are in its
@@ -44,6 +41,10 @@ enum ConvPost : int {
     kPostUnpool    // four times a quarter plus e2, zero where mask is not positive, to e (all double resolution)
 };
 
+// The weights w of one direction of a layer lie as its convolution reads them: per group of 32
+// output channels, chunk of 32 input channels and tap (in the order they are accumulated) and
+// row block h one fragment of 1 KB, lane after lane. Row i of block h is channel
+// 8 (i/4) + 4 h + i % 4 of the group.
 struct ConvArgs {
     const bf16* x;       // input, NHWC
     int xC, xoff, Cin;   // channel stride and offset; input channels, a multiple of 32
