@@ -342,8 +342,8 @@ struct clbm_batch {
     clbm_batch_launch launch;
     const MultiShape* multi;   // deeper tiles in place of the default launch, or nullptr
     int tile_x, tile_y;        // tiles of the list
-    hipGraph_t graph;
-    hipGraphExec_t gexec;
+    hipGraph_t graph[2];        // run graphs from either buffer, all of these arguments
+    hipGraphExec_t gexec[2];
     int graph_K;
     double graph_tol;
     long graph_max;
@@ -436,10 +436,12 @@ clbm_status batch_layout(int n, const clbm_params* p, BatchLayout* L)
 
 void drop_batch_graph(clbm_batch* b)
 {
-    if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->gexec = nullptr;
-    b->graph = nullptr;
+    for (int k = 0; k < 2; ++k) {
+        if (b->gexec[k]) (void)hipGraphExecDestroy(b->gexec[k]);
+        if (b->graph[k]) (void)hipGraphDestroy(b->graph[k]);
+        b->gexec[k] = nullptr;
+        b->graph[k] = nullptr;
+    }
 }
 
 // Rebuild the full tile list and the per-instance tile fields for the current shape.
@@ -608,7 +610,6 @@ clbm_status launch_diag(clbm_batch* b, int compare)
 // Graph: K steps, residual partials, per-instance finalize, compaction (scan, scatter).
 clbm_status build_run_graph(clbm_batch* b, int K, double tol, long max_steps)
 {
-    drop_batch_graph(b);
     hipGraph_t g = nullptr;
     CLBM_HIP(hipGraphCreate(&g, 0));
     hipGraphNode_t prev = nullptr;
@@ -678,8 +679,8 @@ clbm_status build_run_graph(clbm_batch* b, int K, double tol, long max_steps)
         set_last_hip_error(e, "hipGraphInstantiate", __FILE__, __LINE__);
         return CLBM_ERR_HIP;
     }
-    b->graph = g;
-    b->gexec = ex;
+    b->graph[b->parity] = g;
+    b->gexec[b->parity] = ex;
     b->graph_K = K;
     b->graph_tol = tol;
     b->graph_max = max_steps;
@@ -846,7 +847,8 @@ clbm_status clbm_batch_run(clbm_batch* b, long max_steps, double tol, int K, lon
                            long* steps_out, int* status_out)
 {
     if (!b || K < 2 || (K % 2) != 0 || max_steps < 0 || !(tol >= 0.0)) return CLBM_ERR_INVALID_ARG;
-    if (!b->gexec || b->graph_K != K || b->graph_tol != tol || b->graph_max != max_steps) {
+    if (b->graph_K != K || b->graph_tol != tol || b->graph_max != max_steps) drop_batch_graph(b);
+    if (!b->gexec[b->parity]) {   // steps since the last run may have left the state in the other buffer
         clbm_status st = build_run_graph(b, K, tol, max_steps);
         if (st != CLBM_OK) return st;
     }
@@ -855,7 +857,7 @@ clbm_status clbm_batch_run(clbm_batch* b, long max_steps, double tol, int K, lon
     CLBM_HIP(hipStreamSynchronize(b->stream));
     long done = 0;
     while (count > 0 && done < max_steps + K && (budget_steps <= 0 || done < budget_steps)) {
-        CLBM_HIP(hipGraphLaunch(b->gexec, b->stream));
+        CLBM_HIP(hipGraphLaunch(b->gexec[b->parity], b->stream));
         b->step += K;
         done += K;
         CLBM_HIP(hipMemcpyAsync(&count, b->d_count, sizeof(int), hipMemcpyDeviceToHost, b->stream));
