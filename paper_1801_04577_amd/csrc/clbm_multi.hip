@@ -22,9 +22,23 @@ k_multi(const S* __restrict__ src, S* __restrict__ dst, const LatticeConst c, in
                                    steps, inv);
 }
 
+// Waves per SIMD that k_batch_multi is held to: in FP32 with every combination of source
+// terms compiled in, those that the LDS tiles of as many workgroups as fit need, at most six (80
+// registers). Left to itself that variant takes 87 to 95, and of the two workgroups of 32 x 16 tiles on a
+// CU one stays: 16 lattices of 512^2 with none, viscous heating and a field in turn took 84.5 us per step
+// (k_batch_step2: 62.1), now 57.1. The others fit by themselves, and were 7 % slower when held.
+template <typename S, int MODE, int TX, int TY, int NS>
+constexpr int multi_waves_per_eu()
+{
+    typedef MultiTile<TX, TY, NS> T;
+    constexpr int w = (160 * 1024 / (int)(T::elems * sizeof(S)) * (T::NT / 64) + 3) / 4;
+    return MODE != 2 || sizeof(S) == 2 ? 1 : w < 6 ? w : 6;
+}
+
 // The same over the active tile list of a batch; MODE and bands as in k_batch_step2.
 template <typename S, int MODE, int TX, int TY, int NS>
 __global__ void __launch_bounds__((MultiTile<TX, TY, NS>::NT))
+__attribute__((amdgpu_waves_per_eu(multi_waves_per_eu<S, MODE, TX, TY, NS>())))
 k_batch_multi(const BatchInst* __restrict__ insts, const int2* __restrict__ list, const int* __restrict__ count,
               int parity, int bands, int steps, unsigned inv)
 {
