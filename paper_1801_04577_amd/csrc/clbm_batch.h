@@ -9,7 +9,8 @@ struct BatchInst {
     LatticeConst c;
     unsigned long long buf[2];  // device addresses of the two population buffers
     unsigned long long snap;    // device address of the (u_x, u_y, T) snapshot
-    int tiles_x, tile_off, tile_count, pad;
+    int tiles_x[2];             // tiles in a row: of the list, of kBlock columns
+    int tile_off, tile_count;
 };
 
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -21,9 +21,10 @@ namespace clbm {
 
 constexpr int kBP = 6;  // per-tile partials: du2, u2, dT2, T2, bad, max|u|
 
-// One time step of every instance on the active tile list (grid-stride over tiles); S is
-// the storage type of every instance's populations.
-template <typename S>
+// One time step of every instance on a tile list (grid-stride over tiles); S is the
+// storage type of every instance's populations, OWN the index of BatchInst::tiles_x (as an
+// argument, its own load took 1 % of a step).
+template <typename S, int OWN>
 __global__ void __launch_bounds__(1024) k_batch_step(const BatchInst* __restrict__ insts,
                                                      const int2* __restrict__ list,
                                                      const int* __restrict__ count, int parity,
@@ -35,7 +36,7 @@ __global__ void __launch_bounds__(1024) k_batch_step(const BatchInst* __restrict
         const int inst = uniform_int(e.x), tile = uniform_int(e.y);
         const BatchInst& I = insts[inst];
         const LatticeConst c = I.c;
-        const int tiles_x = uniform_int(I.tiles_x);
+        const int tiles_x = uniform_int(I.tiles_x[OWN]);
         const int x = (tile % tiles_x) * tile_x + threadIdx.x;
         // a tile taller than the block is covered by looping over its rows
         for (int ly = threadIdx.y; ly < tile_y; ly += blockDim.y) {
@@ -71,7 +72,7 @@ constexpr int step2_waves_per_eu()
     return w < 4 ? w : 4;
 }
 
-// Two time steps of every instance on the active tile list (tiles of kBlock x TY nodes,
+// Two time steps of every instance on a tile list (tiles of kBlock x TY nodes,
 // NT threads, grid-stride over tiles; the LDS tile is reused by each tile a workgroup
 // takes). Per tile it runs the phases of k_step2, so two steps here are two steps of
 // k_batch_step bit for bit. MODE: 0 = no instance has viscous heating or a source field,
@@ -96,7 +97,7 @@ k_batch_step2(const BatchInst* __restrict__ insts, const int2* __restrict__ list
         const int inst = uniform_int(e.x), id = uniform_int(e.y);
         const BatchInst& I = insts[inst];
         const LatticeConst c = I.c;
-        const int tiles_x = uniform_int(I.tiles_x);
+        const int tiles_x = uniform_int(I.tiles_x[1]);
         const int X0 = (id % tiles_x) * (int)kBlock, Y0 = (id / tiles_x) * TY;
         const S* src = reinterpret_cast<const S*>(I.buf[parity]);
         S* dst = reinterpret_cast<S*>(I.buf[parity ^ 1]);
@@ -156,7 +157,7 @@ __global__ void __launch_bounds__(1024) k_batch_diag(const BatchInst* __restrict
         const int inst = uniform_int(e.x), tile = uniform_int(e.y);
         const BatchInst& I = insts[inst];
         const LatticeConst c = I.c;
-        const int tiles_x = uniform_int(I.tiles_x);
+        const int tiles_x = uniform_int(I.tiles_x[0]);
         const int x = (tile % tiles_x) * tile_x + threadIdx.x;
         double acc[kBP] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         // a tile taller than the block is covered by looping over its rows
@@ -342,6 +343,10 @@ struct clbm_batch {
     clbm_batch_launch launch;
     const MultiShape* multi;   // deeper tiles in place of the default launch, or nullptr
     int tile_x, tile_y;        // tiles of the list
+    int short_tiles;           // multi: tiles of the launch's own shape, listed behind the full list
+                               // with their number as the entry after the last, or 0
+    bool pairs, lone;          // multi: two steps are a launch of its own (multi_pairs), a lone step
+                               // goes over the list's tiles (multi_lone)
     hipGraph_t graph[2];        // run graphs from either buffer, all of these arguments
     hipGraphExec_t gexec[2];
     int graph_K;
@@ -464,7 +469,8 @@ clbm_status apply_shape(clbm_batch* b)
         BatchInst& I = b->inst[i];
         const int tx = (I.c.nx + b->tile_x - 1) / b->tile_x;
         const int ty = (I.c.ny + b->tile_y - 1) / b->tile_y;
-        I.tiles_x = tx;
+        I.tiles_x[0] = tx;
+        I.tiles_x[1] = (I.c.nx + (int)kBlock - 1) / (int)kBlock;
         I.tile_off = off;
         I.tile_count = tx * ty;
         for (int t = 0; t < tx * ty; ++t) b->full_host.push_back(make_int2(i, t));
@@ -472,10 +478,24 @@ clbm_status apply_shape(clbm_batch* b)
     }
     if (off > b->cap_tiles) return CLBM_ERR_INVALID_ARG;
     b->total_tiles = off;
+    b->short_tiles = 0;
+    b->pairs = b->lone = true;
+    const size_t own = tiles(L.tile_x, L.tile_y);
+    if (b->multi && own > 0 && off + own + 1 <= (size_t)b->cap_tiles) {
+        b->short_tiles = (int)own;
+        b->pairs = multi_pairs(*b->multi, nodes, b->precision, b->total_tiles, own);
+        b->lone = multi_lone(*b->multi, nodes, b->precision, b->total_tiles, own * L.tile_x * L.tile_y);
+        for (int i = 0; i < b->n; ++i) {
+            const LatticeConst& c = b->inst[i].c;
+            const int count = (c.nx + L.tile_x - 1) / L.tile_x * ((c.ny + L.tile_y - 1) / L.tile_y);
+            for (int t = 0; t < count; ++t) b->full_host.push_back(make_int2(i, t));
+        }
+        b->full_host.push_back(make_int2(b->short_tiles, 0));
+    }
     CLBM_HIP(hipMemcpyAsync(b->d_inst, b->inst.data(), sizeof(BatchInst) * b->n,
                             hipMemcpyHostToDevice, b->stream));
-    CLBM_HIP(hipMemcpyAsync(b->d_full, b->full_host.data(), sizeof(int2) * off,
-                            hipMemcpyHostToDevice, b->stream));
+    CLBM_HIP(hipMemcpyAsync(b->d_full, b->full_host.data(),
+                            sizeof(int2) * b->full_host.size(), hipMemcpyHostToDevice, b->stream));
     // every instance running, active list = full list
     const int m = std::max(b->n, b->total_tiles);
     hipLaunchKernelGGL(k_batch_reset, dim3((m + 255) / 256), dim3(256), 0, b->stream, b->d_status,
@@ -544,10 +564,11 @@ const void* step2_kernel(const clbm_batch* b)
                                              : step2_for<float>(mix, b->launch.tile_y);
 }
 
+template <int OWN>
 const void* step1_kernel(const clbm_batch* b)
 {
-    return b->precision == CLBM_FP16_SHIFTED ? reinterpret_cast<const void*>(&k_batch_step<__half>)
-                                             : reinterpret_cast<const void*>(&k_batch_step<float>);
+    return b->precision == CLBM_FP16_SHIFTED ? reinterpret_cast<const void*>(&k_batch_step<__half, OWN>)
+                                             : reinterpret_cast<const void*>(&k_batch_step<float, OWN>);
 }
 
 const void* diag_kernel(const clbm_batch* b)
@@ -558,43 +579,45 @@ const void* diag_kernel(const clbm_batch* b)
 
 // Block shape of the one-step and diagnostics kernels (a two-step tile of kBlock x rows
 // nodes is covered by kBlock x min(rows, 16) threads, rows looped).
-dim3 tile_block(const clbm_batch* b)
-{
-    return dim3(b->tile_x, std::min(b->tile_y, 1024 / b->tile_x));
-}
+dim3 tile_block(int tile_x, int tile_y) { return dim3(tile_x, std::min(tile_y, 1024 / tile_x)); }
 
+// Every instance must be on the active list.
 clbm_status launch_batch_steps(clbm_batch* b, int nsteps)
 {
-    if (b->multi && nsteps > 1) {   // a lone step is faster without the ring
-        const StepSplit split(nsteps, b->multi->steps);
-        for (int k = 0; k < split.launches; ++k) {
-            int parity = b->parity, bands = b->launch.xcd_bands, n = split.steps(k);
-            unsigned inv = multi_inv(*b->multi, n);
-            void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &bands, &n, &inv};
-            CLBM_HIP(hipLaunchKernel(b->multi->batch(b->precision, source_mix(b)), step_grid(b),
-                                     dim3(b->multi->threads), args, 0, b->stream));
-            b->step += n;
-            b->parity ^= 1;
-        }
-        return CLBM_OK;
-    }
-    while (nsteps > 0) {
-        if (!b->multi && b->launch.steps_per_launch == 2 && nsteps >= 2) {
-            int parity = b->parity, bands = b->launch.xcd_bands;
-            void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &bands};
-            CLBM_HIP(hipLaunchKernel(step2_kernel(b), step_grid(b), dim3(two_step_threads(b->launch.tile_y)),
-                                     args, 0, b->stream));
-            b->step += 2;
-            nsteps -= 2;
-        } else {
-            int parity = b->parity, tx = b->tile_x, ty = b->tile_y;
-            void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &tx, &ty};
-            CLBM_HIP(hipLaunchKernel(step1_kernel(b), step_grid(b), tile_block(b), args, 0, b->stream));
-            b->step += 1;
-            nsteps -= 1;
-        }
-        CLBM_HIP(hipGetLastError());
+    const int deep = b->multi ? multi_part(*b->multi, b->pairs, nsteps) : 0;
+    const StepSplit split(deep, b->multi ? b->multi->steps : 1);
+    for (int k = 0; k < split.launches; ++k) {
+        int parity = b->parity, bands = b->launch.xcd_bands, n = split.steps(k);
+        unsigned inv = multi_inv(*b->multi, n);
+        void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &bands, &n, &inv};
+        CLBM_HIP(hipLaunchKernel(b->multi->batch(b->precision, source_mix(b)), step_grid(b),
+                                 dim3(b->multi->threads), args, 0, b->stream));
+        b->step += n;
         b->parity ^= 1;
+    }
+    nsteps -= deep;
+    const int2* own = b->d_full + b->total_tiles;   // where listed, its length follows it
+    const int* own_count = &own[b->short_tiles].x;
+    while (nsteps > 0) {
+        const bool pair = b->launch.steps_per_launch == 2 && nsteps >= 2;
+        const bool on_own = b->short_tiles > 0 && (pair || !b->lone);
+        const int2* list = on_own ? own : b->d_active;
+        const int* count = on_own ? own_count : b->d_count;
+        const dim3 grid = on_own ? dim3(b->short_tiles) : step_grid(b);
+        int parity = b->parity, bands = b->launch.xcd_bands;
+        if (pair) {
+            void* args[] = {&b->d_inst, &list, &count, &parity, &bands};
+            CLBM_HIP(hipLaunchKernel(step2_kernel(b), grid, dim3(two_step_threads(b->launch.tile_y)), args, 0,
+                                     b->stream));
+        } else {
+            int tx = on_own ? b->launch.tile_x : b->tile_x, ty = on_own ? b->launch.tile_y : b->tile_y;
+            void* args[] = {&b->d_inst, &list, &count, &parity, &tx, &ty};
+            CLBM_HIP(hipLaunchKernel(on_own ? step1_kernel<1>(b) : step1_kernel<0>(b), grid, tile_block(tx, ty), args, 0, b->stream));
+        }
+        b->step += pair ? 2 : 1;
+        nsteps -= pair ? 2 : 1;
+        b->parity ^= 1;
+        CLBM_HIP(hipGetLastError());
     }
     return CLBM_OK;
 }
@@ -603,7 +626,7 @@ clbm_status launch_diag(clbm_batch* b, int compare)
 {
     int parity = b->parity, tx = b->tile_x, ty = b->tile_y;
     void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &tx, &ty, &compare, &b->d_part};
-    CLBM_HIP(hipLaunchKernel(diag_kernel(b), step_grid(b), tile_block(b), args, 0, b->stream));
+    CLBM_HIP(hipLaunchKernel(diag_kernel(b), step_grid(b), tile_block(b->tile_x, b->tile_y), args, 0, b->stream));
     return CLBM_OK;
 }
 
@@ -613,7 +636,7 @@ clbm_status build_run_graph(clbm_batch* b, int K, double tol, long max_steps)
     hipGraph_t g = nullptr;
     CLBM_HIP(hipGraphCreate(&g, 0));
     hipGraphNode_t prev = nullptr;
-    const dim3 blk = tile_block(b);
+    const dim3 blk = tile_block(b->tile_x, b->tile_y);
     const dim3 grid = step_grid(b);
     int parity = b->parity, bands = b->launch.xcd_bands;
     int tx = b->tile_x, ty = b->tile_y;
@@ -624,8 +647,9 @@ clbm_status build_run_graph(clbm_batch* b, int K, double tol, long max_steps)
     int pairs = 0, singles = K;
     if (b->multi) {
         const StepSplit split(K, b->multi->steps, true);
-        singles = 0;
-        for (int k = 0; k < split.launches && st == CLBM_OK; ++k) {
+        // two lone steps are faster without the ring
+        singles = split.steps(0) == 1 ? K : 0;
+        for (int k = 0; singles == 0 && k < split.launches && st == CLBM_OK; ++k) {
             int n = split.steps(k);
             unsigned inv = multi_inv(*b->multi, n);
             void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &bands, &n, &inv};
@@ -643,7 +667,7 @@ clbm_status build_run_graph(clbm_batch* b, int K, double tol, long max_steps)
     }
     for (int k = 0; k < singles && st == CLBM_OK; ++k) {
         void* args[] = {&b->d_inst, &b->d_active, &b->d_count, &parity, &tx, &ty};
-        st = add_node(g, &prev, step1_kernel(b), grid, blk, args);
+        st = add_node(g, &prev, step1_kernel<0>(b), grid, blk, args);
         parity ^= 1;
     }
     int compare = 1;

@@ -251,17 +251,43 @@ const MultiShape* multi_shape(Tiles tiles, size_t nodes, int precision)
     return nullptr;
 }
 
-// How many of n steps a lattice takes in launches of m; the others take the one- and two-step
+// Whether two steps that are left of a call are a launch of m too, not one of the two-step
+// kernel. On large lattices it pays the ring and hides less: FP32, two-step kernel first, 1000 x 777
+// 25 and 26 us, 1400^2 50 and 54, 2800^2 171 and 193, but 800 x 600 20 and 17; FP16 1200^2 32 and 34,
+// 1000 x 777 20 and 24 the other way round. A batch gives its tile counts too (else 0): of 32 x 16 nodes,
+// which collide 1124 for two steps, and of 64 x 14 for the two-step kernel, 1952, each node 3 % faster
+// in FP32 and 10 % in FP16. Calls of two steps, two-step kernel first, FP32: 6 lattices of 700^2 (deeper
+// tiles 1.3 % more nodes) 88 and 91 us, 16 of 512^2 (0.4 % fewer) 124 and 126, 64 from 64^2 to 505^2 (4 %
+// fewer) 207 and 191; FP16: 8 of 330^2 (8 % fewer) 32 and 36, 24 from 64 x 60 to 156 x 129 (12 % fewer)
+// 25 and 20.
+inline bool multi_pairs(const MultiShape& m, size_t nodes, int precision, size_t tiles = 0, size_t two_step_tiles = 0)
+{
+    const bool half = precision == CLBM_FP16_SHIFTED;
+    if (m.steps != 3) return true;
+    if (tiles > 0 && (half || nodes > (size_t)5 << 17))
+        return (half ? 1.1 : 1.03) * 1124 * (double)tiles < 1952.0 * (double)two_step_tiles;
+    return nodes <= (half ? (size_t)1 << 20 : (size_t)5 << 17);
+}
+
+// Whether a lone step of a batch goes over the tiles of m, not over those of the two-step kernel
+// (`nodes2` places in them): less of small tiles lies outside the lattices, but their short rows cost in
+// FP16 and where there is little to hide them. The two-step kernel's tiles first: FP32 24 lattices
+// of 96^2 (27 % fewer places) 18 and 16 us, 8 of 330^2 35 and 33, 64 from 64^2 to 505^2 159 and 150, but
+// 4 of 300^2 (1 % fewer) 20 and 21; FP16 the first 16 and 14, the last 16 and 18.
+inline bool multi_lone(const MultiShape& m, size_t nodes, int precision, size_t tiles, size_t nodes2)
+{
+    if (precision != CLBM_FP16_SHIFTED && nodes > (size_t)5 << 17) return true;
+    return 1.15 * (double)(tiles * m.tx * m.ty) < (double)nodes2;
+}
+
+// How many of n steps are taken in launches of m; the others take the one- and two-step
 // kernels (all of them give the same bits). A lone step is always theirs: 1000 x 777 in FP32
-// 17.5 against 20.3 us, 1200^2 26 against 32. On large lattices so is a launch of two steps, which
-// pays the ring and hides less: 1000 x 777 25 against 26 us, 1400^2 50 against 54, 2800^2
-// 171 against 193 (but 800 x 600 20 against 17; FP16: 1200^2 32 against 34, 1000 x 777 24
-// against 20), so that only whole launches of three are left, and four steps are two pairs.
-inline int multi_part(const MultiShape& m, size_t nodes, int precision, int n)
+// 17.5 against 20.3 us, 1200^2 26 against 32. Without pairs only whole launches of three are
+// left, and four steps are two pairs.
+inline int multi_part(const MultiShape& m, bool pairs, int n)
 {
     if (n < 2) return 0;
-    if (m.steps != 3 || nodes <= (precision == CLBM_FP16_SHIFTED ? (size_t)1 << 20 : (size_t)5 << 17)) return n;
-    return n - (n % 3 == 1 ? 4 : n % 3);
+    return pairs ? n : n - (n % 3 == 1 ? 4 : n % 3);
 }
 
 // n steps as launches of at most `most` steps, as even as they come.

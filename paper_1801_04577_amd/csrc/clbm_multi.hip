@@ -53,7 +53,7 @@ k_batch_multi(const BatchInst* __restrict__ insts, const int2* __restrict__ list
         const int inst = uniform_int(e.x), id = uniform_int(e.y);
         const BatchInst& I = insts[inst];
         const LatticeConst c = I.c;
-        const int tiles_x = uniform_int(I.tiles_x);
+        const int tiles_x = uniform_int(I.tiles_x[0]);
         const int X0 = (id % tiles_x) * TX, Y0 = (id / tiles_x) * TY;
         const S* src = reinterpret_cast<const S*>(I.buf[parity]);
         S* dst = reinterpret_cast<S*>(I.buf[parity ^ 1]);

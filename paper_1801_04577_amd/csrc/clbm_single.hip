@@ -449,7 +449,7 @@ const MultiShape* multi_of(const clbm_handle* h)
 
 int deep_steps(const clbm_handle* h, const MultiShape* m, int n)
 {
-    return m ? multi_part(*m, (size_t)h->c.nx * h->c.ny, h->p.precision, n) : 0;
+    return m ? multi_part(*m, multi_pairs(*m, (size_t)h->c.nx * h->c.ny, h->p.precision), n) : 0;
 }
 
 // The launches of n steps: launches of the deeper tiles, then two-step launches while two or

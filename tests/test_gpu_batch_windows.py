@@ -59,3 +59,28 @@ def assert_no_slower(sizes, sources, precision, call, calls):
 @pytest.mark.parametrize("sizes", [[(330, 330)] * 8, [(512, 512)] * 16, [(64 + 7 * i, 64 + 7 * i) for i in range(64)]])
 def test_mixed_sources(sizes):
     assert_no_slower(sizes, ["", "viscous", "field"], 0, lambda b: b.step(20), 10)
+
+
+@pytest.mark.parametrize("sizes,precision,call", [
+    ([(300, 300)] * 4, 1, lambda b: b.step(1)), ([(300, 300)] * 4, 1, lambda b: b.step(2)),
+    ([(330, 330)] * 8, 1, lambda b: b.step(2)), ([(330, 330)] * 8, 1, lambda b: b.step(4)),
+    ([(512, 512)] * 16, 0, lambda b: b.step(2)), ([(64 + 4 * i, 60 + 3 * i) for i in range(24)], 1, lambda b: b.step(2)),
+    ([(512, 512)] * 16, 0, lambda b: b.run(40, 0.0, K=2))])
+def test_short_windows(sizes, precision, call):
+    assert_no_slower(sizes, [""], precision, call, 40)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("sizes", [[(64, 2), (40, 3)], [(300, 300)] * 4, [(700, 640)] * 3])
+def test_short_windows_keep_the_state(sizes, precision):
+    """Calls that mix deeper launches with pairs and lone steps over the second tile list, and
+    lists too small for it, against two-step launches: the same bits."""
+    import torch
+    sources = ["", "viscous", "field"]
+    own, two = batch(sizes, sources, precision, None), batch(sizes, sources, precision, TWO_STEP)
+    for n in (1, 2, 4, 7, 8, 1, 3, 5):
+        own.step(n)
+        two.step(n)
+        for i in range(own.n):
+            for x, y in zip(own.macros(i), two.macros(i)):
+                assert torch.equal(x, y), (n, i)
