@@ -24,7 +24,8 @@ struct MultiTile {
     static constexpr int R = NS - 1;                          // ring of the first of NS phases
     static constexpr int XE = TX + 2 * R, YE = TY + 2 * R;    // LDS tile with the ring
     static constexpr unsigned P = XE * YE;                    // LDS population stride
-    static constexpr unsigned elems = (NS > 2 ? 2 : 1) * 14 * P;
+    static_assert(NS > 1, "one step per launch is k_step");
+    static constexpr unsigned elems = 2 * 14 * P;             // two tiles: ring r writes tile r % 2
     static constexpr int NT = (XE * YE + 63) / 64 * 64;       // a thread per node of the first phase
 };
 
@@ -206,7 +207,7 @@ __device__ __forceinline__ void multi_tile(const S* __restrict__ src, S* __restr
     // no node that a phase advances lies at a wall, and nothing wraps
     const bool interior = X0 >= steps && X0 + TX - 1 + steps < c.nx && Y0 >= steps && Y0 + TY - 1 + steps < c.ny;
     multi_first<S, SRC, TX, TY, NS>(src, dst, c, lds, X0, Y0, tid, steps - 1, inv, interior);
-    if constexpr (NS > 1) multi_rest<S, SRC, TX, TY, NS, NS - 2>(dst, c, lds, X0, Y0, tid, steps, interior);
+    multi_rest<S, SRC, TX, TY, NS, NS - 2>(dst, c, lds, X0, Y0, tid, steps, interior);
 }
 
 // ---------------------------------------------------------------------------
