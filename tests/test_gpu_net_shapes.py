@@ -78,3 +78,46 @@ def test_resample_widths(sh, sw, dh, dw, nf):
     want = want * np.array(scale)[:, None, None] + np.array(shift)[:, None, None]
     big = np.abs(s).max() * max(scale) + max(shift)
     assert np.abs(got - want).max() <= 2.0 ** -24 * (8 + 8 * (sh + sw)) * big
+
+
+# What the cases above do not reach: eight rows per wave (images and batches that give every SIMD two
+# waves) with each epilogue, tiles of two waves by two channel groups and those over 64 KB of LDS, layers
+# whose tile does not fit in LDS at all (more than 455 input channels, four blocks of pixels per wave),
+# the output layer from 32 channels to more than four and from 480, rings of 512 pixels and rings
+# per kernel row where rows are no multiple of 32.
+LARGE_CASES = [
+    (32, 64, 64, 8, 3, (64, 128, 32, 32)),
+    (16, 64, 64, 8, 3, (128, 64, 32, 32)),
+    (512, 16, 16, 8, 3, (64, 32, 32, 32)),
+    (48, 64, 64, 8, 3, (32, 192, 32, 32)),
+    (16, 96, 80, 8, 5, (32, 64, 128, 256)),
+    (16, 16, 176, 8, 3, (32, 128, 32, 32)),
+    (16, 16, 208, 3, 4, (64, 32, 32, 32)),
+    (32, 16, 24, 4, 4, (480, 32, 32, 32)),
+]
+
+
+@pytest.mark.parametrize("B,H,W,cin,cout,widths", LARGE_CASES)
+def test_large_shapes_elementwise(B, H, W, cin, cout, widths):
+    test_shapes_elementwise(B, H, W, cin, cout, widths)
+
+
+@pytest.mark.parametrize("cout", [4, 5])
+def test_output_layer_from_many_channels(cout):
+    """480 channels to the output, whose tile does not fit in LDS. The outputs only, in the same unit:
+    64 pixels of 32 channels at the coarsest level are too few for the gradients' bound (the reference
+    with BF16 storage lies 15 units from the one without there, and the gradients 10 from either)."""
+    import torch
+    import paper_1801_04577_amd as clbm
+    B, H, W, cin, widths = 16, 16, 16, 4, (480, 32, 32, 32)
+    rng = np.random.default_rng(cout)
+    params = [(w.astype(np.float32).astype(np.float64),
+               rng.normal(scale=0.05, size=b.shape).astype(np.float32).astype(np.float64))
+              for w, b in ref.init_params(cin, cout, widths, seed=3)]
+    xs = rng.normal(size=(B, cin, H, W)).astype(np.float32)
+    n = clbm.Net(B, H, W, cin, cout, widths)
+    n.set_params(torch.from_numpy(np.concatenate([np.concatenate([w.reshape(-1), b]) for w, b in params])
+                                  .astype(np.float32)))
+    y = n.forward(torch.from_numpy(xs)).cpu().numpy().astype(np.float64)
+    want = np.stack([ref.forward(params, x.astype(np.float64), quant=True) for x in xs])
+    assert worst(y, want) <= 4.0
