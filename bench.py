@@ -482,6 +482,49 @@ def small_configs(args):
     return out
 
 
+def steps_text(spl):
+    """How the steps of a lattice are launched, for the workload's description."""
+    return "%d step(s)" % spl if spl <= 2 else "up to %s steps" % {3: "three", 4: "four", 6: "six"}.get(spl, spl)
+
+
+def step_roofline(args, s, spl, nodes, ev_ms, copy_gbs):
+    """The bandwidth account of the one- and two-step launches of a timed region of ev_ms (HIP
+    events on the solver's stream). The launches of the library's smaller tiles, of a
+    varying number of steps each and from the caches, have none."""
+    import torch
+    launches = launches_of(args.steps, spl)
+    kms = ev_ms / launches
+    kms_iso, _ = kernel_avg_ms(torch, s, args.kernel_launches)
+    bpl = BYTES_PER_LUP[args.precision]
+    must_move = bpl * nodes                       # every population read once, written once
+    achieved = must_move / (kms * 1e-3) / 1e9
+    effective = bpl * nodes * spl / (kms * 1e-3) / 1e9
+    log("bench: step kernel %.4f ms per launch of %d step(s), %d launches (%.4f ms over %d back-to-back launches), "
+        "%.0f GB/s moved, %.0f GB/s per-step algorithmic"
+        % (kms, spl, launches, kms_iso, args.kernel_launches, achieved, effective))
+    traffic = measured_traffic(args.precision, args.n, spl)
+    valu = measured_valu(args.precision, args.n, spl)
+    return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+            "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
+            "traffic": traffic,
+            "bytes_per_launch": must_move,
+            "kernel": "k_step2" if spl == 2 else "k_step", "steps_per_launch": spl,
+            "kernel_avg_ms": round(kms, 5), "launches_timed": launches,
+            "kernel_avg_ms_back_to_back": round(kms_iso, 5),
+            # measured HBM bytes over the same launch time
+            "traffic_rate_GBs": None if traffic is None else round(traffic / (kms * 1e-3) / 1e9, 1),
+            # one-step updates the launch performs, at the one-step kernel's bytes each
+            "effective_GBs": round(effective, 1), "bytes_per_lup": bpl,
+            "copy_ceiling_GBs": round(copy_gbs, 1),
+            "frac_of_copy": round(achieved / copy_gbs, 4),
+            "note": ("achieved = bytes one launch must move (each of the %d B per node read once and "
+                     "written once) / launch time from HIP events around the timed region; a launch "
+                     "advances %d step(s), so the per-step algorithmic rate is effective_GBs"
+                     % (bpl, spl)),
+            # the kernel's VALU issue from the committed counter profile
+            "valu": valu}
+
+
 def batched_sweep(args):
     """The batched form on the 256-cavity sweep: autotuned one-launch-per-step over a
     device tile list, against a loop of per-cavity launches of the single-lattice step on
@@ -1039,22 +1082,10 @@ def main():
     wall, ev_ms, diags = time_steps(torch, s, args.steps, args.diag_every)
     nodes = args.n * args.n
     mlups = nodes * args.steps / wall / 1e6
-    spl = s.get_launch()["steps_per_launch"]
-    launches = launches_of(args.steps, spl)
-    kms = ev_ms / launches           # the timed region's launches, HIP events on the solver's stream
-    log("bench: %.4f ms/step, %.1f MLUPS; %d launches, %.4f ms per launch (events), %d diagnostics"
-        % (wall / args.steps * 1e3, mlups, launches, kms, diags))
-    kms_iso, _ = kernel_avg_ms(torch, s, args.kernel_launches)
-    d = s.diagnostics()
-    bpl = BYTES_PER_LUP[args.precision]
-    must_move = bpl * nodes                       # every population read once, written once
-    achieved = must_move / (kms * 1e-3) / 1e9
-    effective = bpl * nodes * spl / (kms * 1e-3) / 1e9
-    log("bench: step kernel %.4f ms per launch of %d step(s) (%.4f ms over %d back-to-back launches), "
-        "%.0f GB/s moved, %.0f GB/s per-step algorithmic, nan %d"
-        % (kms, spl, kms_iso, args.kernel_launches, achieved, effective, d.nan_count))
-    traffic = measured_traffic(args.precision, args.n, spl)
-    valu = measured_valu(args.precision, args.n, spl)
+    log("bench: %.4f ms/step, %.1f MLUPS, %d diagnostics" % (wall / args.steps * 1e3, mlups, diags))
+    spl = s.steps_per_launch()
+    roofline = None if spl > 2 else step_roofline(args, s, spl, nodes, ev_ms, copy_gbs)
+    log("bench: %d non-finite values" % s.diagnostics().nan_count)
     if diags:
         diag_text = "the diagnostics reduction after every %d steps (%d calls in the timed region)" % (
             args.diag_every, diags)
@@ -1067,37 +1098,15 @@ def main():
         "dtype": arithmetic_dtype(args.precision),
         "data": "synthetic",
         "config": {"workload": "cavity %dx%d Ra=1e6 Pr=0.71 Q=5e-6 U=0.1, %s populations, "
-                               "fused collide-and-stream, %d step(s) per launch, %s replayed from graphs "
+                               "fused collide-and-stream, %s per launch, %s replayed from graphs "
                                "of %d steps, %s"
-                               % (args.n, args.n, args.precision, spl, "steps" if gsteps else "no steps",
+                               % (args.n, args.n, args.precision, steps_text(spl), "steps" if gsteps else "no steps",
                                   gsteps, diag_text),
                    "nx": args.n, "ny": args.n, "storage": args.precision,
                    "collision_arithmetic": arithmetic_dtype(args.precision),
                    "launch": s.get_launch(), "graph_steps": gsteps, "diagnostics_calls": diags},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic,
-                     "bytes_per_launch": must_move,
-                     "kernel": "k_step2" if spl == 2 else "k_step", "steps_per_launch": spl,
-                     "kernel_avg_ms": round(kms, 5), "launches_timed": launches,
-                     "kernel_avg_ms_back_to_back": round(kms_iso, 5),
-                     # measured HBM bytes over the same launch time
-                     "traffic_rate_GBs": None if traffic is None else round(traffic / (kms * 1e-3) / 1e9, 1),
-                     # one-step updates the launch performs, at the one-step kernel's bytes each
-                     "effective_GBs": round(effective, 1), "bytes_per_lup": bpl,
-                     "copy_ceiling_GBs": round(copy_gbs, 1),
-                     "frac_of_copy": round(achieved / copy_gbs, 4),
-                     "note": ("achieved = bytes one launch must move (each of the %d B per node read once and "
-                              "written once) / launch time from HIP events around the timed region; a launch "
-                              "advances %d step(s), so the per-step algorithmic rate is effective_GBs"
-                              % (bpl, spl)),
-                     # the kernel's VALU issue from the committed counter profile
-                     "valu": valu},
+        "roofline": roofline,
     }
-    if not args.launch and nodes <= (3 << 19 if args.precision == "fp16s" else 1 << 23):
-        # smaller lattices run up to six steps per launch from the caches: no launch to account for
-        out["roofline"] = None
-        out["config"]["workload"] = out["config"]["workload"].replace("%d step(s)" % spl, "up to six steps")
     if not args.no_cpu_baseline:
         log("bench: timing the FP64 oracle on the host")
         out["cpu_baseline"] = cpu_baseline(prob)

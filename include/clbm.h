@@ -222,6 +222,9 @@ clbm_status clbm_load(clbm_handle* h, const void* d_src, long step);
 clbm_status clbm_get_step(const clbm_handle* h, long* step);
 clbm_status clbm_set_launch(clbm_handle* h, const clbm_launch* launch);
 clbm_status clbm_get_launch(const clbm_handle* h, clbm_launch* launch);
+/* The most time steps that one launch takes under the present launch shape: 1, 2, or up to six
+ * where the library takes its own tiles. */
+clbm_status clbm_steps_per_launch(const clbm_handle* h, int* steps);
 /* A heat source given per node, added to the uniform Q (Sec. 3.2 treats a spatially
  * variable source; Eq. (23)-(25) take the node's source): d_q is a device float32
  * array [ny][nx] (row-major, x fastest) that the caller owns and keeps alive and

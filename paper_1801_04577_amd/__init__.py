@@ -114,6 +114,7 @@ def _declare(L):
         "clbm_get_step": (st, [_VP, ctypes.POINTER(ctypes.c_long)]),
         "clbm_set_launch": (st, [_VP, ctypes.POINTER(clbm_launch)]),
         "clbm_get_launch": (st, [_VP, ctypes.POINTER(clbm_launch)]),
+        "clbm_steps_per_launch": (st, [_VP, ctypes.POINTER(ctypes.c_int)]),
         "clbm_set_graph": (st, [_VP, ctypes.c_int]),
         "clbm_set_source_field": (st, [_VP, _VP]),
         "clbm_batch_set_source_field": (st, [_VP, ctypes.c_int, _VP]),
@@ -372,6 +373,12 @@ class Solver:
         return {"block_x": L.block_x, "block_y": L.block_y, "rows_per_thread": L.rows_per_thread,
                 "xcd_remap": L.xcd_remap, "steps_per_launch": L.steps_per_launch,
                 "two_step_rows": L.two_step_rows}
+
+    def steps_per_launch(self):
+        """The most time steps that one launch takes under the present launch shape."""
+        n = ctypes.c_int()
+        _check(lib().clbm_steps_per_launch(self._h, ctypes.byref(n)), "clbm_steps_per_launch")
+        return n.value
 
     def set_graph(self, steps_per_graph):
         _check(lib().clbm_set_graph(self._h, int(steps_per_graph)), "clbm_set_graph")

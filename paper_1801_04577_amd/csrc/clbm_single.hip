@@ -876,6 +876,14 @@ clbm_status clbm_get_launch(const clbm_handle* h, clbm_launch* launch)
     return CLBM_OK;
 }
 
+clbm_status clbm_steps_per_launch(const clbm_handle* h, int* steps)
+{
+    if (!h || !steps) return CLBM_ERR_INVALID_ARG;
+    const MultiShape* m = multi_of(h);
+    *steps = m ? m->steps : h->launch.steps_per_launch;
+    return CLBM_OK;
+}
+
 clbm_status clbm_set_source_field(clbm_handle* h, const float* d_q)
 {
     if (!h) return CLBM_ERR_INVALID_ARG;
