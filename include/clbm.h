@@ -176,7 +176,9 @@ clbm_status clbm_init_from_fields(clbm_handle* h, const float* d_rho, const floa
  * wall rules of Sec. 3 and Eq. (26)-(28), all fused per node as listed at the top of
  * this file. One fused kernel per step, or one per two steps when steps_per_launch = 2;
  * steps are replayed from a HIP graph when graphs are enabled. nsteps = 0 is a no-op,
- * nsteps < 0 (or a NULL handle) returns CLBM_ERR_INVALID_ARG.
+ * nsteps < 0 (or a NULL handle) returns CLBM_ERR_INVALID_ARG. Steps recorded into a stream
+ * capture of the caller's can be replayed any number of times where nsteps is a multiple of
+ * four (with steps_per_launch = 1 of two): the state is then in the same buffer before and after.
  * Asynchronous; CLBM_ERR_HIP if a launch fails. */
 clbm_status clbm_step(clbm_handle* h, int nsteps);
 

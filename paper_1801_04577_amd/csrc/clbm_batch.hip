@@ -585,7 +585,10 @@ dim3 tile_block(int tile_x, int tile_y) { return dim3(tile_x, std::min(tile_y, 1
 clbm_status launch_batch_steps(clbm_batch* b, int nsteps)
 {
     const int deep = b->multi ? multi_part(*b->multi, b->pairs, nsteps) : 0;
-    const StepSplit split(deep, b->multi ? b->multi->steps : 1);
+    StepSplit split(deep, b->multi ? b->multi->steps : 1);
+    const int as_pairs = (two_step_launches(nsteps) - two_step_launches(nsteps - deep)) % 2;
+    if (deep && split.launches % 2 != as_pairs && is_captured(b->stream))
+        split = StepSplit(deep, b->multi->steps, as_pairs);
     for (int k = 0; k < split.launches; ++k) {
         int parity = b->parity, bands = b->launch.xcd_bands, n = split.steps(k);
         unsigned inv = multi_inv(*b->multi, n);
@@ -646,7 +649,7 @@ clbm_status build_run_graph(clbm_batch* b, int K, double tol, long max_steps)
     // in place of one of them when K/2 is odd, or an even number of deeper launches.
     int pairs = 0, singles = K;
     if (b->multi) {
-        const StepSplit split(K, b->multi->steps, true);
+        const StepSplit split(K, b->multi->steps, 0);
         // two lone steps are faster without the ring
         singles = split.steps(0) == 1 ? K : 0;
         for (int k = 0; singles == 0 && k < split.launches && st == CLBM_OK; ++k) {

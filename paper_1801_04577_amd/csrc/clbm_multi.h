@@ -291,18 +291,33 @@ inline int multi_part(const MultiShape& m, bool pairs, int n)
     return pairs ? n : n - (n % 3 == 1 ? 4 : n % 3);
 }
 
-// n steps as launches of at most `most` steps, as even as they come.
+// n steps as launches of at most `most` steps, as even as they come; parity 0 or 1: an even or odd
+// number of launches (of n > 1 steps).
 struct StepSplit {
     int launches, base, extra;   // the first `extra` launches take base + 1 steps
-    StepSplit(int n, int most, bool even_launches = false)
+    StepSplit(int n, int most, int parity = -1)
     {
         launches = (n + most - 1) / most;
-        if (even_launches && launches % 2 != 0) ++launches;
+        if (parity >= 0 && launches % 2 != parity) ++launches;
         base = launches ? n / launches : 0;
         extra = launches ? n % launches : 0;
     }
     int steps(int k) const { return base + (k < extra ? 1 : 0); }
 };
+
+// Launches of n steps by the two-step kernel.
+inline int two_step_launches(int n) { return n / 2 + n % 2; }
+
+// Whether steps issued now are recorded into a caller's stream capture. The recorded launches
+// start from one of two buffers and can be repeated only if they end in it too. With the two-step
+// kernel that held for every multiple of four steps, and launches of the deeper tiles are
+// recorded in a number of the same parity; where steps run at once it does not matter.
+inline bool is_captured(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    // (the null stream cannot be captured)
+    return stream && hipStreamIsCapturing(stream, &status) == hipSuccess && status == hipStreamCaptureStatusActive;
+}
 
 // The divisor of multi_first for launches of `steps` steps.
 inline unsigned multi_inv(const MultiShape& m, int steps)

@@ -447,24 +447,36 @@ const MultiShape* multi_of(const clbm_handle* h)
         (size_t)c.nx * c.ny, h->p.precision);
 }
 
-int deep_steps(const clbm_handle* h, const MultiShape* m, int n)
-{
-    return m ? multi_part(*m, multi_pairs(*m, (size_t)h->c.nx * h->c.ny, h->p.precision), n) : 0;
-}
-
 // The launches of n steps: launches of the deeper tiles, then two-step launches while two or
-// more steps remain (when enabled), then single steps. Calls emit(fn, grid, block, args)
-// for each.
+// more steps remain (when enabled), then single steps. as_pairs: as many, modulo 2, as
+// without the deeper tiles.
+struct StepPlan {
+    int n;
+    const MultiShape* m;
+    int deep;            // steps of the deeper tiles
+    StepSplit split;
+    int launches;        // in all
+    StepPlan(const clbm_handle* h, int steps, bool as_pairs)
+        : n(steps),
+          m(multi_of(h)),
+          deep(m ? multi_part(*m, multi_pairs(*m, (size_t)h->c.nx * h->c.ny, h->p.precision), n) : 0),
+          split(deep, m ? m->steps : 1, deep && as_pairs ? (two_step_launches(n) - two_step_launches(n - deep)) % 2 : -1),
+          launches(split.launches + (h->launch.steps_per_launch == 2 ? two_step_launches(n - deep) : n - deep))
+    {
+    }
+};
+
+// Calls emit(fn, grid, block, args) for each launch.
 template <typename Emit>
-clbm_status plan_steps(clbm_handle* h, int n, int from, Emit emit)
+clbm_status plan_steps(clbm_handle* h, const StepPlan& plan, int from, Emit emit)
 {
-    const MultiShape* m = multi_of(h);
-    int cur = from;
-    if (const int deep = deep_steps(h, m, n)) {
+    const MultiShape* m = plan.m;
+    int cur = from, n = plan.n;
+    if (const int deep = plan.deep) {
         const void* fn = m->single(h->p.precision, lattice_src(h->c));
         int tiles_x = (h->c.nx + m->tx - 1) / m->tx, total = tiles_x * ((h->c.ny + m->ty - 1) / m->ty);
         const dim3 grid((unsigned)align_up((size_t)total, 8), 1, 1), block(m->threads, 1, 1);
-        const StepSplit split(deep, m->steps);
+        const StepSplit& split = plan.split;
         for (int k = 0; k < split.launches; ++k, cur ^= 1) {
             void *src = h->buf[cur], *dst = h->buf[cur ^ 1];
             int steps = split.steps(k);
@@ -505,22 +517,17 @@ clbm_status plan_steps(clbm_handle* h, int n, int from, Emit emit)
     return CLBM_OK;
 }
 
-// Number of launches (buffer flips) of n steps.
-int launches_of(const clbm_handle* h, int n)
-{
-    const MultiShape* m = multi_of(h);
-    const int deep = deep_steps(h, m, n), rest = n - deep;
-    return (deep ? StepSplit(deep, m->steps).launches : 0) + (h->launch.steps_per_launch == 2 ? rest / 2 + rest % 2 : rest);
-}
-
 clbm_status launch_steps_direct(clbm_handle* h, int n)
 {
-    clbm_status st = plan_steps(h, n, h->cur, [&](const void* fn, dim3 g, dim3 b, void** args) {
+    StepPlan plan(h, n, false);
+    if (plan.deep && (plan.launches - two_step_launches(n)) % 2 != 0 && is_captured(h->stream))
+        plan = StepPlan(h, n, true);
+    clbm_status st = plan_steps(h, plan, h->cur, [&](const void* fn, dim3 g, dim3 b, void** args) {
         CLBM_HIP(hipLaunchKernel(fn, g, b, args, 0, h->stream));
         return CLBM_OK;
     });
     if (st != CLBM_OK) return st;
-    h->cur ^= launches_of(h, n) & 1;
+    h->cur ^= plan.launches & 1;
     h->step += n;
     return CLBM_OK;
 }
@@ -531,7 +538,8 @@ clbm_status build_graph(clbm_handle* h, int start)
     CLBM_HIP(hipGraphCreate(&g, 0));
     hipGraphNode_t prev = nullptr;
     // hipGraphAddKernelNode copies the argument values.
-    clbm_status st = plan_steps(h, h->graph_steps, start, [&](const void* fn, dim3 gd, dim3 bd, void** args) {
+    const StepPlan plan(h, h->graph_steps, false);
+    clbm_status st = plan_steps(h, plan, start, [&](const void* fn, dim3 gd, dim3 bd, void** args) {
         hipKernelNodeParams kp;
         std::memset(&kp, 0, sizeof kp);
         kp.func = const_cast<void*>(fn);
@@ -693,7 +701,7 @@ clbm_status clbm_step(clbm_handle* h, int nsteps)
                 if (st != CLBM_OK) return st;
             }
             CLBM_HIP(hipGraphLaunch(h->gexec[h->cur], h->stream));
-            h->cur ^= launches_of(h, h->graph_steps) & 1;
+            h->cur ^= StepPlan(h, h->graph_steps, false).launches & 1;
             h->step += h->graph_steps;
             left -= h->graph_steps;
         }
