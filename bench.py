@@ -526,8 +526,8 @@ def step_roofline(args, s, spl, nodes, ev_ms, copy_gbs):
 
 
 def batched_sweep(args):
-    """The batched form on the 256-cavity sweep: autotuned one-launch-per-step over a
-    device tile list, against a loop of per-cavity launches of the single-lattice step on
+    """The batched form on the 256-cavity sweep: autotuned launches over a device tile
+    list, against a loop of per-cavity launches of the single-lattice step on
     the same cavities; then a run of every cavity to its residual (--sweep-tol, 1e-7 by
     default; FP16 storage needs a tolerance above its rounding-noise floor of about 1e-6)
     with on-device retirement (graph of K steps + convergence check + tile-list
@@ -560,7 +560,7 @@ def batched_sweep(args):
     torch.cuda.synchronize()
     t_batch = time.perf_counter() - t0
     mlups_batch = nodes * args.sweep_steps / t_batch / 1e6
-    log("batched: %.1f MLUPS (one launch per step)" % mlups_batch)
+    log("batched: %.1f MLUPS" % mlups_batch)
     # the same cavities advanced one launch per cavity per step
     solvers = []
     for p, f in zip(probs, inits):

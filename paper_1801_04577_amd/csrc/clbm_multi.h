@@ -234,9 +234,9 @@ const MultiShape* multi_shapes();
 //   256^2: 4.5, 32x8 2.13, 32x12 2.38    384^2: 4.8, 32x8 4.8, 32x12 3.26, 32x16 3.8
 //   512^2: 6.6, 32x12 4.5, 32x16 4.1    1500^2: 29.4, 32x12 27.9, 32x16 25.8
 //  2048^2: 49.2, 32x16 45.5            4096^2: 179, 32x16 175
-// The lattices beyond 2^23 nodes stay with two steps per launch: 2 % is left there, and their
-// launches are what the bandwidth and counter figures of the two-step kernel are taken from.
-// In FP16 the two-step kernel's taller tile wins from about 1.6 million nodes:
+// 2^23 nodes is how far the shapes are taken, not where they stop to pay: 32x16 is the faster one beyond it
+// too (3200^2 110.7 and 106.8, 4096^2 177.5 and 173.6, 6000^2 381 and 373; 256 cavities of 64 to 512 a
+// side, 28.8 million nodes, 389 and 331). In FP16 the two-step kernel's taller tile wins from about 1.6 million nodes:
 //   512^2: 6.0, 32x16 4.0   1200^2: 15.8, 32x16 14.2   1400^2: 18.8, 32x16 19.0   2048^2: 34.6, 32x16 38.3
 template <typename Tiles>
 const MultiShape* multi_shape(Tiles tiles, size_t nodes, int precision)

@@ -22,7 +22,7 @@ def test_captured_steps_of_a_lattice(nx, ny, precision):
     import torch
     import paper_1801_04577_amd as clbm
     prob, stream = W.cavity(nx, ny, Ra=1e4, Pr=0.71), torch.cuda.Stream()
-    for n in (4, 8, 16, 20, 28, 100):
+    for n in (3, 4, 7, 8, 16, 20, 28, 100):
         with torch.cuda.stream(stream):
             s, alone = clbm.Solver(prob, precision, stream=stream), clbm.Solver(prob, precision, stream=stream)
             for v in (s, alone):
@@ -45,7 +45,7 @@ def test_captured_steps_of_a_batch(sizes, precision):
     import torch
     import paper_1801_04577_amd as clbm
     probs, stream = [W.cavity(nx, ny, Ra=1e4, Pr=0.71) for nx, ny in sizes], torch.cuda.Stream()
-    for n in (4, 8, 16, 20, 28, 100):
+    for n in (3, 4, 7, 8, 16, 20, 28, 100):
         with torch.cuda.stream(stream):
             b = clbm.Batch(probs, precision=precision, stream=stream)
             alone = [clbm.Solver(p, precision, stream=stream) for p in probs]
